@@ -390,6 +390,231 @@ static void build_blocks(const pa_solver *s, Plan &p, int direct)
         }
 }
 
+bool pa_host::fuse_draws(int n, int n_levels, int dmax)
+{
+    return dmax <= 8 && n >= 256 * n_levels;
+}
+
+// The tile form's item streams and blocks (their layout is described at
+// sweep_tile_kernel). Every level is cut into items of at most 64 lanes, dealt over the
+// waves; levels are gathered into chunks whose draws fit half the draw buffer,
+// and the draws of a chunk are dealt, as items of 64 slots, into the places
+// that the chunk before it leaves free.
+static void build_tile_plan(const pa_solver *s, Plan &p)
+{
+    const int n = s->n, W = p.W, nw = p.threads / 64;
+    const bool d16 = p.deg == 2;
+    auto degree = [&](int slot) {
+        const int i = p.sched[slot];
+        return s->row_ptr[i + 1] - s->row_ptr[i];
+    };
+    // Entries a lane's block holds: 6 + 8 + 8 after a short header, 4 in the
+    // first row after a long one, 16 in all with sign bits, the first row
+    // alone with draws in registers. A node of a larger degree takes 2^lp
+    // lanes. An item that leaves half its lanes free spreads its nodes over
+    // more of them down to one row a lane: the chain of a level shortens with
+    // the entries read in turn.
+    const bool long_head = p.fuse || p.bsg != 0;
+    const int e0 = long_head ? 4 : 6;
+    const int most = p.fuse ? e0 : p.bsg == 2 ? 16 : e0 + 16, lp_max = d16 ? 6 : 4;
+    struct Item {
+        int slot, count, lp, rows;
+    };
+    std::vector<Item> cut;
+    std::vector<int> level_item(p.n_levels + 1, 0);
+    for (int l = 0; l < p.n_levels; ++l) {
+        for (int t = p.level_off[l]; t < p.level_off[l + 1];) {
+            const int md = degree(t);
+            auto per_lane = [&](int lp) { return (md + (1 << lp) - 1) >> lp; };
+            Item it{t, 0, 0, 1};
+            while (per_lane(it.lp) > most) ++it.lp;
+            it.count = std::min(p.level_off[l + 1] - t, 64 >> it.lp);
+            while (it.lp < lp_max && per_lane(it.lp) > e0 && it.count << (it.lp + 1) <= 64) ++it.lp;
+            const int e = per_lane(it.lp);
+            it.rows = e <= e0 ? 1 : 1 + (e - e0 + 7) / 8;
+            cut.push_back(it);
+            t += it.count;
+        }
+        level_item[l + 1] = (int)cut.size();
+    }
+    p.n_rounds = 0;
+    for (int l = 0; l < p.n_levels; ++l) p.n_rounds += (level_item[l + 1] - level_item[l] + nw - 1) / nw;
+
+    // Chunks: runs of items whose slots fit a half of the draw buffer.
+    const int cap = pa::tile_draw_slots(W, d16) / 128 * 64;
+    p.draw_half = cap * (d16 ? 2 * W : W);
+    std::vector<int> chunk_item{0};             // first item of each chunk, then the end
+    for (int c = 0, slot = 0; c < (int)cut.size(); ++c)
+        if (!p.fuse && cut[c].slot + cut[c].count - slot > cap) {
+            chunk_item.push_back(c);
+            slot = cut[c].slot;
+        }
+    chunk_item.push_back((int)cut.size());
+    const int n_chunks = (int)chunk_item.size() - 1;
+    auto chunk_slot = [&](int c) { return c < n_chunks ? cut[chunk_item[c]].slot : n; };
+
+    // An item's wave: a level's items are dealt to the waves in turn; where
+    // its item would stand alone (or nearly: at most a quarter more items than
+    // levels) wave 0 takes the levels by itself and needs no barrier between.
+    const bool solo = nw >= 2 && (long long)cut.size() * 4 <= 5LL * p.n_levels;
+    std::vector<int> item_wave(cut.size(), 0);
+    for (int l = 0, c = 1; l < p.n_levels && !solo; ++l)
+        for (int q = level_item[l], k = 0; q < level_item[l + 1]; ++q) {
+            if (q == chunk_item[c]) {           // a chunk's first item
+                ++c;
+                k = 0;
+            }
+            item_wave[q] = k++ % nw;
+        }
+
+    // Blocks: the draw items' nodes, then the levels' rows.
+    const int rec_words = 8;            // u16 per lane and row
+    std::vector<int> draw_at(n_chunks, 0);      // uint4 offset of a chunk's draw blocks
+    std::vector<int> draw_items(n_chunks, 0);
+    size_t u4 = 0;
+    if (!p.fuse)
+        for (int c = 0; c < n_chunks; ++c) {
+            draw_at[c] = (int)u4;
+            draw_items[c] = (chunk_slot(c + 1) - chunk_slot(c) + 63) / 64;
+            u4 += 64 * (size_t)draw_items[c];
+        }
+    std::vector<int> block_at(cut.size());
+    for (size_t c = 0; c < cut.size(); ++c) {
+        block_at[c] = (int)u4;
+        u4 += (size_t)cut[c].rows * ((cut[c].count << cut[c].lp) + 1);
+    }
+    u4 += 2 * 65;                               // rows that the last items do not have
+    std::vector<uint16_t> b16(u4 * rec_words, 0);
+    for (int c = 0; c < (p.fuse ? 0 : n_chunks); ++c)
+        for (int t = 0; t < 64 * draw_items[c]; ++t) {
+            uint16_t *b = &b16[((size_t)draw_at[c] + t) * rec_words];
+            const int slot = chunk_slot(c) + t;
+            b[0] = slot < chunk_slot(c + 1) ? (uint16_t)p.sched[slot] : 0;
+        }
+    for (size_t c = 0; c < cut.size(); ++c) {
+        const Item &it = cut[c];
+        const int lanes = it.count << it.lp;
+        auto at = [&](int row, int lane) -> uint16_t * {
+            return &b16[((size_t)block_at[c] + (size_t)row * (lanes + 1) + lane) * rec_words];
+        };
+        const int dummy = pa::tile_record(W, p.fuse, (p.bsg == 1 ? 2 * n : n) + item_wave[c]);
+        for (int r = 0; r < it.rows; ++r)
+            for (int q = 0; q < rec_words; ++q) at(r, lanes)[q] = (uint16_t)dummy;
+        uint16_t *spare = at(0, lanes);
+        spare[1] = 0;
+        if (long_head) {
+            spare[2] = 0;
+            spare[3] = p.bsg == 1 ? (uint16_t)dummy : 0;
+        }
+        for (int lane = 0; lane < lanes; ++lane) {
+            const int i = p.sched[it.slot + (lane >> it.lp)], part = lane & ((1 << it.lp) - 1);
+            const int first = s->row_ptr[i], d = s->row_ptr[i + 1] - first;
+            const int per = (degree(it.slot) + (1 << it.lp) - 1) >> it.lp;
+            const int own = pa::tile_record(W, p.fuse, i);
+            for (int r = 0; r < it.rows; ++r)
+                for (int q = 0; q < rec_words; ++q) at(r, lane)[q] = (uint16_t)own;
+            uint16_t *h = at(0, lane);
+            h[1] = (uint16_t)d;
+            if (long_head) {
+                h[2] = (uint16_t)i;
+                h[3] = p.bsg == 1 ? (uint16_t)pa::tile_record(W, p.fuse, n + i) : 0;
+            }
+            for (int q = part * per; q < std::min(d, (part + 1) * per); ++q) {
+                const int t = q - part * per;
+                const int j = s->col[first + q];
+                const bool neg = q >= s->npos[i];
+                const uint16_t rec =
+                    (uint16_t)pa::tile_record(W, p.fuse, p.bsg == 1 && neg ? n + j : j);
+                // (A short header's third and fourth u16 are its entries 4 and 5.)
+                if (t < 4) h[4 + t] = rec;
+                else if (t < e0) h[t - 2] = rec;
+                else at(1 + (t - e0) / 8, lane)[(t - e0) % 8] = rec;
+                if (p.bsg == 2 && neg) h[3] = (uint16_t)(h[3] | 1u << t);
+            }
+        }
+    }
+    p.blocks.assign(b16.size() / 2, 0u);
+    std::memcpy(p.blocks.data(), b16.data(), b16.size() * sizeof(uint16_t));
+    p.block_bytes = 16;
+
+    // Streams. An interval runs from barrier to barrier: a level, or a run of
+    // levels that wave 0 takes by itself.
+    struct Interval {
+        std::vector<std::vector<int2>> wave;    // items of each wave
+    };
+    std::vector<std::vector<int2>> st(nw);
+    std::vector<Interval> iv;
+    int wave0_run = 0;                          // the open interval is wave 0's alone
+    auto open_interval = [&](int alone) {
+        iv.push_back(Interval{std::vector<std::vector<int2>>(nw)});
+        wave0_run = alone;
+    };
+    auto size_of = [&](const Interval &v) {
+        size_t m = 0;
+        for (const auto &w : v.wave) m = std::max(m, w.size());
+        return m;
+    };
+    for (int c = 0, l = 0; c < n_chunks; ++c) {
+        iv.clear();
+        for (int q = chunk_item[c]; q < chunk_item[c + 1];) {
+            while (level_item[l + 1] <= q) ++l;
+            const int end = std::min(level_item[l + 1], chunk_item[c + 1]);
+            const int alone = solo || level_item[l + 1] - level_item[l] == 1;
+            if (iv.empty() || !(alone && wave0_run)) open_interval(alone);
+            for (; q < end; ++q) {
+                const Item &it = cut[q];
+                iv.back().wave[item_wave[q]].push_back(
+                    int2{block_at[q] * 16, pa::item_word(it.count << it.lp, p.fuse ? 0 : it.slot - chunk_slot(c),
+                                                         it.rows, it.lp, 1)});
+            }
+        }
+        if (!p.fuse) {
+            // The next chunk's draws, each where it lengthens its interval
+            // least (wave 0 last).
+            const int c2 = c + 1 < n_chunks ? c + 1 : 0, kind = c + 1 < n_chunks ? 2 : 3;
+            for (int t = 0; t < draw_items[c2]; ++t) {
+                std::vector<int2> *best = nullptr;
+                long long best_cost = 0;
+                for (Interval &v : iv) {
+                    const long long longest = (long long)size_of(v);
+                    for (int w = nw - 1; w >= 0; --w) {
+                        const long long len = (long long)v.wave[w].size() + 1;
+                        const long long cost = len > longest ? (1LL << 32) + len : len - longest;
+                        if (!best || cost < best_cost) {
+                            best = &v.wave[w];
+                            best_cost = cost;
+                        }
+                    }
+                }
+                best->push_back(int2{(draw_at[c2] + 64 * t) * 16, pa::item_word(63, 64 * t, 1, 0, kind)});
+            }
+        }
+        for (size_t v = 0; v < iv.size(); ++v) {
+            const bool chunk_end = v + 1 == iv.size(), sweep_end = chunk_end && c + 1 == n_chunks;
+            // (The sweep's last barrier is the kernel's own.)
+            const int flags = (sweep_end ? 0 : pa::kItemBarrier) | (chunk_end && !p.fuse ? pa::kItemChunk : 0);
+            for (int w = 0; w < nw; ++w) {
+                auto &it = iv[v].wave[w];
+                if (flags != 0) {
+                    if (it.empty()) it.push_back(int2{0, pa::item_word(0, 0, 1, 0, 0)});
+                    it.back().y |= pa::item_word(0, 0, 1, 0, flags);
+                }
+                st[w].insert(st[w].end(), it.begin(), it.end());
+            }
+        }
+    }
+    p.items.clear();
+    p.streams.clear();
+    for (int w = 0; w < nw; ++w) {
+        std::vector<int2> &it = st[w];
+        if (it.size() & 1) it.push_back(int2{0, pa::item_word(0, 0, 1, 0, 0)});
+        const size_t len = it.size();
+        p.streams.insert(p.streams.end(), {(int)p.items.size() / 2, (int)len, draw_at[0], draw_items[0]});
+        for (int q = 0; q < 3; ++q) it.push_back(len ? it[q % len] : int2{0, pa::item_word(0, 0, 1, 0, 0)});
+        for (const int2 &v : it) p.items.insert(p.items.end(), {v.x, v.y});
+    }
+}
+
 // floor(2^32 * exp(-(beta * 2m))): the acceptance threshold of an uphill
 // flip raising E by 2m at inverse temperature beta.
 static uint64_t threshold_fixed(double beta, int m)
@@ -434,8 +659,118 @@ static void parallel_rows(int K, long long work, const std::function<void(int, i
     for (auto &th : pool) th.join();
 }
 
+int Plan::sweep_lds(const pa_solver *s) const
+{
+    if (kind == 2) return pa::sweep_lds_bytes(W, sgn, s->n, s->dmax, threads);
+    if (ahead) return pa::sweep_tile_lds(W, bsg == 1 ? 1 : 0, s->n, fuse);
+    return pa::sweep_bytes_lds(W, bsg == 1 ? 1 : 0, s->n, s->dmax);
+}
+
+// Workspace bytes of the parts that depend on the sweep kernel's form: its
+// plan, its threshold rows and what a workgroup leaves behind.
+static size_t tail_bytes(const pa_solver *s, const Plan &p, size_t thr)
+{
+    return align_up(thr * (size_t)p.K * p.lmax1 * (s->dmax + 1)) + align_up(sizeof(uint64_t) * p.nblk) +
+           align_up(sizeof(uint32_t) * (size_t)p.nblk * p.nw32);
+}
+
+static size_t general_bytes(const pa_solver *s, const Plan &p)
+{
+    const int n = s->n;
+    size_t blocks, stream = 0;
+    if (p.kind == 1) {
+        const int need = 4 * ((std::max(s->dmax, 1) + 3) / 4);
+        int capk = 6;
+        while (capk < need) capk += 8;
+        blocks = 4 * (((size_t)(n + p.threads) * (2 + capk) + 32 + 1) / 2);
+        for (int l = 0; l < p.n_levels; ++l)
+            stream += 16 * (size_t)((p.level_off[l + 1] - p.level_off[l] + p.threads - 1) / p.threads);
+    } else {
+        const int NS = 64 / p.W, NW = p.threads / 64;
+        blocks = 4 * ((size_t)n * (4 + 4 * ((std::max(s->dmax, 1) + 3) / 4)) + 32);
+        size_t passes = 0;
+        for (int l = 0; l < p.n_levels; ++l)
+            passes += (size_t)((p.level_off[l + 1] - p.level_off[l] + NW * NS - 1) / (NW * NS));
+        stream = 8 * (size_t)NW * (passes + 4);
+    }
+    return align_up(sizeof(int) * n) + align_up(sizeof(int) * (p.n_levels + 1)) + align_up(blocks) +
+           align_up(stream) + tail_bytes(s, p, sizeof(uint64_t));
+}
+
+static size_t tile_bytes(const pa_solver *s, const Plan &p)
+{
+    return align_up(sizeof(uint32_t) * p.blocks.size()) + align_up(sizeof(int) * p.items.size()) +
+           align_up(sizeof(int) * p.streams.size()) + tail_bytes(s, p, sizeof(uint32_t));
+}
+
+// Whether a run takes the tile form, and its shape then; p comes with the
+// general form's choice and the levels. All figures: one step of 10 sweeps on
+// MI355X, microseconds.
+static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, int cus, int max_lds)
+{
+    const int n = s->n, tile = sch->tile_replicas;
+    const bool sign_ok = n + 256 <= 0x7FFF;
+    if (p.sgn && !sign_ok) return false;
+    const int was_kind = p.kind, was_W = p.W;
+    const bool was_turns = p.kind == 1 && p.W == 8 && p.nblk > cus && p.nblk <= 2 * cus;
+    const long long per_level = n / p.n_levels;     // nodes a level, on average
+    p.kind = 1;
+    p.ahead = 1;
+    p.deg = degree_class(s->dmax);
+    // Negative edges read complemented copies of the records (no work per
+    // neighbour), or carry sign bits in the blocks (two instructions per
+    // neighbour and 8 replicas, half the LDS): sign bits at low degrees and
+    // where two workgroups with copies would not share a compute unit.
+    p.bsg = !p.sgn ? 0
+            : s->dmax <= 8 || p.deg != 0 || 2 * pa::sweep_tile_lds(8, 1, n, 0) > max_lds ? 2 : 1;
+    const int comp = p.bsg == 1 ? 1 : 0;
+    p.fuse = p.bsg != 1 && tile != 16 && fuse_draws(n, p.n_levels, s->dmax);
+    auto lds = [&](int W) { return pa::sweep_tile_lds(W, comp, n, p.fuse); };
+    // Shape. A sweep is a chain of levels, so it takes as long for one
+    // workgroup as for all that are resident: the narrowest tile whose
+    // workgroups get a compute unit each, and else 8 replicas (R = 1,024 on a
+    // 100 x 100 torus: 125 with 4, 172 with 8; R = 2,048: 228 and 184). 16
+    // where 8 would take more than one generation of four and levels are
+    // small (n = 800, degree 12, R = 16,384: 257 with 16, 317 with 8; n =
+    // 4,000: 926 and 873).
+    p.W = tile;
+    if (p.deg == 2) p.W = 4;
+    else if (tile == 0) {
+        p.W = (p.R + 3) / 4 <= cus ? 4 : 8;
+        if (!p.fuse && (p.R + 7) / 8 > 4 * cus && per_level <= 100 && 4 * lds(16) <= max_lds) p.W = 16;
+    }
+    if (lds(p.W) > max_lds) return false;
+    p.nblk = (p.R + p.W - 1) / p.W;
+    if (sch->wg_threads == 0) {
+        // A compute unit holds 16 of this kernel's waves; a workgroup takes
+        // its share of them (n = 4,000, degree 12, R = 16,384, four resident:
+        // 873 with 256 threads, 1,145 with 512; R = 1,024, one resident, 100 x
+        // 100 torus: 125 with 1,024, 140 with 512). Small levels have no use
+        // for more than 512 threads (n = 800: 123 with either), levels of
+        // thousands of nodes none for less (the torus at R = 8,192: 625 with
+        // 512, 677 with 256).
+        const int need = (p.nblk + cus - 1) / cus, res = std::min(need, max_lds / lds(p.W));
+        p.threads = res == 1 ? (per_level >= 100 ? 1024 : 512) : res == 2 || per_level >= 1000 ? 512 : 256;
+    }
+    // Form. The tile form shortens the chain of a level, and long rows spread
+    // over lanes (n = 800, R = 1,024: 187 -> 131 at degree 12, 2,870 -> 380
+    // at 48, where rows run past the general form's registers; degree 200 on
+    // 1,000 nodes, the word kernel before: 47,440 -> 1,770), and its nibble
+    // records let 8 replicas stand where bytes leave room for 4 (n = 12,000,
+    // R = 4,096, degree 12: 843 -> 562). The general form keeps levels of
+    // many nodes, which fill its waves without drawing ahead: above about 350
+    // with 4 replicas (n = 20,000, degree 6, R = 1,024: 373 and 372; 467 a
+    // level: 158 and 165), above 256 with more (n = 7,000 in colouring order,
+    // 778 a level, R = 4,096: 264 and 306), and above 192 with its two
+    // workgroups a compute unit in issue-priority turns (n = 7,000, degree 12,
+    // 212 a level, R = 4,096: 408 and 412).
+    if (was_kind == 2 || p.fuse || s->dmax > kBytesRegDegree) return true;
+    if (was_W == 4 && p.W == 8 && p.nblk >= 2 * cus && 2 * lds(8) <= max_lds) return true;
+    return per_level <= (was_W == 4 ? 350 : was_turns ? 192 : 256);
+}
+
 pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan &p, bool tables,
-                              const Shape *force)
+                              const Shape *force, size_t room)
 {
     const int n = s->n;
     p.K = sch->n_steps;
@@ -513,6 +848,11 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
     bool bytes_ok = s->dmax <= kMaxBytesDegree && (tile == 0 || tile <= 16) && !partial_sat && idx_fit;
     if (req == 1 && !bytes_ok)
         return fail(PA_EINVAL, "sweep kernel 1 needs max degree <= %d and tile 4, 8 or 16", kMaxBytesDegree);
+    // The tile form serves degrees up to kMaxWideDegree; explicitly requested
+    // kernels and tiles keep kernel 1's documented range.
+    const bool tile_ok = req != 2 && !partial_sat && (tile == 0 || tile <= 16) &&
+                         (s->dmax <= kMaxBytesDegree ||
+                          (req == 0 && s->dmax <= kMaxWideDegree && (tile == 0 || tile == 4)));
     if (force) {
         // A shape imposed by a multi-run launch: kernel 1 with the given tile,
         // threads, record mode and entry form, or an error.
@@ -614,7 +954,19 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
                 break;
             }
     }
-    build_blocks(s, p, -1);
+    // The tile form where it is faster, and where the workspace has room for
+    // it: its plan can be the larger one.
+    if (tile_ok && room != 0) {
+        const size_t general = general_bytes(s, p);
+        Plan q = p;
+        if (take_tile_form(s, sch, q, cus, max_lds)) {
+            build_tile_plan(s, q);
+            const size_t own = tile_bytes(s, q);
+            p = std::move(q);
+            p.pad = general > own ? general - own : 0;
+        }
+    }
+    if (!p.ahead) build_blocks(s, p, -1);
     if (p.kind == 1) {
         // Two workgroups sharing a compute unit: the issue arbiter breaks
         // ties by age, so the one dispatched first would finish far earlier
@@ -625,7 +977,7 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
         // 840k / 850k), the launch 7 % shorter. Launches of several
         // generations of workgroups (the 100 x 100 torus) were 2 % slower
         // with the slots alternating, so they keep the plain kernel.
-        const int lds = pa::sweep_bytes_lds(p.W, p.bsg == 1 ? 1 : 0, n, s->dmax);
+        const int lds = p.sweep_lds(s);
         const int waves = (p.threads + 63) / 64;
         const int per_cu = std::min(max_lds / std::max(lds, 1), 16 / std::max(waves, 1));
         const long long slots = (long long)cus * per_cu;
@@ -737,11 +1089,12 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
     L.npos = take(sizeof(int) * n);
     L.edges = take(sizeof(uint32_t) * s->edges.size());
     L.qtab = sch->nl_period > 0 && sch->nl_kind == 1 ? take(sizeof(uint64_t) * (size_t)p.K * p.lmax1) : 0;
-    L.sched = take(sizeof(int) * n);
-    L.level_off = take(sizeof(int) * (p.n_levels + 1));
+    L.sched = p.ahead ? 0 : take(sizeof(int) * n);
+    L.level_off = p.ahead ? 0 : take(sizeof(int) * (p.n_levels + 1));
     L.blocks = take(sizeof(uint32_t) * p.blocks.size());
-    L.stream = take(sizeof(int) * (p.kind == 1 ? p.rounds.size() : p.stream.size()));
-    L.thr = take(sizeof(uint64_t) * (size_t)p.K * p.lmax1 * (s->dmax + 1));
+    L.stream = take(sizeof(int) * (p.ahead ? p.items.size() : p.kind == 1 ? p.rounds.size() : p.stream.size()));
+    L.streams = p.ahead ? take(sizeof(int) * p.streams.size()) : 0;
+    L.thr = take((p.ahead ? sizeof(uint32_t) : sizeof(uint64_t)) * (size_t)p.K * p.lmax1 * (s->dmax + 1));
     L.wtab = take(sizeof(uint64_t) * (size_t)total);
     L.wtab_off = take(sizeof(int) * p.K);
     L.wtab_len = take(sizeof(int) * p.K);
@@ -763,7 +1116,13 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
     L.parent = take(sizeof(int) * p.Rp);
     L.counts = (p.record & 1) ? take(sizeof(int) * (size_t)p.K * R) : 0;
     L.xinit = (p.record & 2) ? take(sizeof(uint64_t) * (size_t)p.G * n) : 0;
-    L.total = o;
+    // What a run needs is no less with one form than with the other, so a
+    // workspace that was too small stays so.
+    L.total = o + p.pad;
+    if (p.ahead && L.total > room) {
+        p = Plan();
+        return build_plan(s, sch, R, p, tables, nullptr, 0);
+    }
     return PA_OK;
 }
 
@@ -835,7 +1194,7 @@ pa_status pa_host::start_run(pa_solver *s, const pa_schedule *sch, int32_t R, ui
     s->has_run = false;
     s->rc.valid = false;          // until this run's state is complete in the workspace
     Plan p;
-    st = build_plan(s, sch, R, p, true, force);
+    st = build_plan(s, sch, R, p, true, force, workspace_bytes);
     if (st != PA_OK) return st;
     if (workspace_bytes < p.L.total)
         return fail(PA_EWORKSPACE, "workspace of %zu bytes < %zu needed", workspace_bytes, p.L.total);
@@ -879,10 +1238,15 @@ pa_status pa_host::start_run(pa_solver *s, const pa_schedule *sch, int32_t R, ui
     put(L.col, s->col.data(), sizeof(int) * s->nnz);
     put(L.npos, s->npos.data(), sizeof(int) * n);
     put(L.edges, s->edges.data(), sizeof(uint32_t) * s->edges.size());
-    put(L.sched, P.sched.data(), sizeof(int) * n);
-    put(L.level_off, P.level_off.data(), sizeof(int) * (P.n_levels + 1));
+    if (!P.ahead) {
+        put(L.sched, P.sched.data(), sizeof(int) * n);
+        put(L.level_off, P.level_off.data(), sizeof(int) * (P.n_levels + 1));
+    }
     put(L.blocks, P.blocks.data(), sizeof(uint32_t) * P.blocks.size());
-    if (P.kind == 1)
+    if (P.ahead) {
+        put(L.stream, P.items.data(), sizeof(int) * P.items.size());
+        put(L.streams, P.streams.data(), sizeof(int) * P.streams.size());
+    } else if (P.kind == 1)
         put(L.stream, P.rounds.data(), sizeof(int) * P.rounds.size());
     else
         put(L.stream, P.stream.data(), sizeof(int) * P.stream.size());
@@ -993,6 +1357,9 @@ pa_status pa_host::start_run(pa_solver *s, const pa_schedule *sch, int32_t R, ui
     sa.n_rounds = P.n_rounds;
     sa.flush_every = P.flush_every;
     sa.direct = P.direct;
+    sa.items = reinterpret_cast<const int2 *>(ws + L.stream);
+    sa.streams = reinterpret_cast<const int4 *>(ws + L.streams);
+    sa.draw_half = P.draw_half;
     sa.prio_mode = P.prio_mode;
     sa.R = R;
     sa.S = P.S;
@@ -1088,7 +1455,11 @@ static pa_status run_range(pa_solver *s, int k0, int k1)
             sa.X = reinterpret_cast<uint64_t *>(ws + Xn);
             sa.E = reinterpret_cast<int *>(ws + En);
             sa.parent = c.parents_pending ? reinterpret_cast<const int *>(ws + L.parent) : nullptr;
-            LAUNCH_TRY(pa::launch_sweep_bytes(P.W, P.bsg, P.threads, P.nblk, sa, hs));
+            if (P.ahead)
+                LAUNCH_TRY(pa::launch_sweep_tile(P.W, P.bsg, P.deg, P.fuse, P.threads, P.nblk, P.sweep_lds(s), sa,
+                                                 hs));
+            else
+                LAUNCH_TRY(pa::launch_sweep_bytes(P.W, P.bsg, P.threads, P.nblk, sa, hs));
             std::swap(Xc, Xn);
             std::swap(Ec, En);
             c.parents_pending = false;
@@ -1225,7 +1596,7 @@ extern "C" pa_status pa_run_static(pa_solver *s, const pa_schedule *sch, int32_t
     if (st != PA_OK) return st;
     if (instance > 65535) return fail(PA_ERANGE, "instance=%u outside [0, 65535]", instance);
     Plan p;
-    st = build_plan(s, sch, R, p, false);
+    st = build_plan(s, sch, R, p, false, nullptr, pa::kStaticScratchBytes);
     if (st != PA_OK) return st;
     if (p.L.total > pa::kStaticScratchBytes)
         return fail(PA_EWORKSPACE, "run needs %zu workspace bytes, more than the %zu of the static "
@@ -1513,8 +1884,7 @@ extern "C" pa_status pa_get_launch_info(pa_solver *s, int64_t out[8])
     out[1] = P.W;
     out[2] = P.threads;
     out[3] = P.nblk;
-    out[4] = P.kind == 1 ? pa::sweep_bytes_lds(P.W, P.bsg == 1 ? 1 : 0, s->n, s->dmax)
-                         : pa::sweep_lds_bytes(P.W, P.sgn, s->n, s->dmax, P.threads);
+    out[4] = P.sweep_lds(s);
     out[5] = P.n_levels;
     out[6] = P.kind == 1 ? P.n_rounds : P.qpad - 4;
     out[7] = P.K;

@@ -60,6 +60,10 @@ struct SweepArgs {
     int direct;                 // kernel 1: block entries are LDS byte offsets
     int prio_mode;              // kernel 1: 1 = issue-priority turns of the two workgroups
                                 // sharing a compute unit (8-replica tiles), else 0
+    // Tile form of kernel 1 (see sweep_tile in pa_kernels.hip).
+    const int2 *items;          // per wave: {block offset in bytes, item_word}, then its first three again
+    const int4 *streams;        // [waves] {first item, items, block (uint4) and count of the first draws}
+    int draw_half;              // bytes of a half of the draw buffer
     const uint64_t *thr;        // kernel 2: [K][lmax1][dmax+1] T[m] (T[0] unused), by grid point
     const uint32_t *thr32;      // kernel 1: [K][lmax1][dmax+1] T[1..dmax], all-accept flag
     const int *as_state;        // [0] level, [3] grid point of this step
@@ -151,6 +155,21 @@ int sweep_lds_bytes(int W, int sgn, int n, int dmax, int threads);
 int launch_sweep(int W, int sgn, int threads, int nblk, const SweepArgs &a, void *stream);
 int sweep_bytes_lds(int W, int sgn, int n, int dmax);
 int launch_sweep_bytes(int W, int sgn, int threads, int nblk, const SweepArgs &a, void *stream);
+// Tile form: number (LDS address / record size) of record x, LDS bytes of a
+// workgroup (comp: complemented copies; fuse: no draw buffer), slots of the
+// draw buffer, and the launch (sg: record mode; deg: 0 degrees up to 63, 1 up
+// to 127, 2 16-bit counters).
+int tile_record(int W, int fuse, int x);
+int sweep_tile_lds(int W, int comp, int n, int fuse);
+int tile_draw_slots(int W, int deg16);
+// The second word of an item: its last lane, first slot in the draw buffer,
+// rows of 16 bytes a lane (1..3), lanes per node (log2) and kind: 0 nothing,
+// 1 decide, 2 draw for this sweep, 3 draw for the next; + kItemBarrier where
+// a barrier follows, + kItemChunk where the next chunk begins.
+constexpr int kItemBarrier = 4, kItemChunk = 8;
+int item_word(int last, int slot, int rows, int lp, int kind);
+int launch_sweep_tile(int W, int sg, int deg, int fuse, int threads, int nblk, int lds, const SweepArgs &a,
+                      void *stream);
 int launch_epilogue(const EpiArgs &a, void *stream);
 // Multi-run launches: `blocks` workgroups over the work list {run, tile}
 // (sgn 0 unsigned records, 2 sign bits; `lds` the largest run's sweep LDS),

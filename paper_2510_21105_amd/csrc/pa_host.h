@@ -35,6 +35,8 @@ pa_status hip_fail(hipError_t e, const char *what);
 constexpr int kMaxN = 32767;   // node ids and LDS word indices fit 16 bits
 constexpr int kMaxDegree = 4096;
 constexpr int kMaxBytesDegree = 127;   // byte counters of kernel 1 (2u must fit a byte)
+constexpr int kBytesRegDegree = 30;    // row entries that the byte form keeps in registers
+constexpr int kMaxWideDegree = 1023;   // 16-bit counters of the tile form: 64 lanes x 16 entries
 constexpr int kMaxR = 32768;
 constexpr size_t kAlign = 256;
 
@@ -42,7 +44,7 @@ inline size_t align_up(size_t b, size_t a = kAlign) { return (b + a - 1) / a * a
 
 struct Layout {
     // Host inputs, uploaded together: [0, inputs_end).
-    size_t row_ptr, col, npos, edges, qtab, sched, level_off, blocks, stream, thr, wtab, wtab_off,
+    size_t row_ptr, col, npos, edges, qtab, sched, level_off, blocks, stream, streams, thr, wtab, wtab_off,
         wtab_len, inputs_end;
     size_t vout;
     size_t X0, X1, E0, E1, cand, snap, counters, as_state, best, best_x, stats, parent;
@@ -56,15 +58,22 @@ struct Plan {
     int direct = 0;   // kernel 1: block entries are LDS byte offsets (else record indices)
     int prio_mode = 0;  // kernel 1: issue-priority turns (SweepArgs::prio_mode)
     int bsg = 0;      // kernel 1 records: 0 unsigned, 1 complemented copies, 2 sign bits in entries
+    int ahead = 0;    // kernel 1: the tile form (sweep_tile_kernel), which draws ahead, and:
+    int deg = 0;      //   counters: 0 degrees up to 63, 1 up to 127, 2 16 bits
+    int fuse = 0;     //   draws in registers, no draw buffer
+    int draw_half = 0;  // SweepArgs::draw_half
+    size_t pad = 0;     // bytes of the workspace left over at its end
     std::vector<int> sched, level_off;
     std::vector<uint32_t> blocks;   // [n][block_bytes / 4] + 128 B
     std::vector<int> stream;        // kernel 2: [waves][qpad][2]
     std::vector<int> rounds;        // kernel 1: [n_rounds][4]
+    std::vector<int> items, streams;    // tile form: SweepArgs::items, streams
     std::vector<uint64_t> thr, wtab;
     std::vector<uint32_t> thr32;   // kernel 1: [K][lmax1][dmax + 1] = T[1..dmax], saturation flag
     std::vector<uint64_t> qtab;    // single-replica cluster moves: [K][lmax1] bond thresholds
     std::vector<int> wtab_off, wtab_len;
     Layout L{};
+    int sweep_lds(const pa_solver *s) const;   // LDS bytes of a sweep workgroup
 };
 
 // A launch shape imposed on kernel 1 (multi-run launches share one shape):
@@ -74,9 +83,16 @@ struct Shape {
     int W = 8, threads = 512, bsg = 0, direct = 1;
 };
 
+// Counter class of the tile form for a maximum degree.
+inline int degree_class(int dmax) { return dmax <= 63 ? 0 : dmax <= 127 ? 1 : 2; }
+// Whether a sweep of n nodes in n_levels dependency levels draws in registers.
+bool fuse_draws(int n, int n_levels, int dmax);
+
 pa_status check_schedule(const pa_solver *s, const pa_schedule *sch, int R);
+// room: workspace bytes at hand (a form that needs more than another is passed
+// over then; 0: the general forms only).
 pa_status build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan &p, bool tables,
-                     const Shape *force = nullptr);
+                     const Shape *force = nullptr, size_t room = (size_t)-1);
 uint64_t run_key(const pa_solver *s, const pa_schedule *sch, int32_t R, uint64_t seed, uint32_t instance);
 pa_status start_run(pa_solver *s, const pa_schedule *sch, int32_t R, uint64_t seed, uint32_t instance,
                     void *workspace, size_t workspace_bytes, void *stream, bool fresh, bool pinned = true,

@@ -15,10 +15,13 @@
 // of the sweep order at a time (those nodes are pairwise non-adjacent), with a
 // barrier between levels -- the same result as the sequential sweep.
 //
-//   sweep_bytes_kernel (kernel 1, default): one lane = one node for all W = 4,
-//     8 or 16 replicas, spins as byte records, bytewise neighbour counts.
+//   sweep_tile_kernel (kernel 1, tile form): lanes = nodes of a level for all
+//     W = 4, 8 or 16 replicas, spins as byte or nibble records; draws are made
+//     ahead of the levels that use them.
+//   sweep_bytes_kernel (kernel 1, byte form): one lane = one node, spins as
+//     byte records, draws made in the level; for levels of many nodes.
 //   sweep_kernel (kernel 2): one lane = one replica, W = 16, 32 or 64 replicas
-//     as bit words; for degrees above 127 and as an independent check.
+//     as bit words; for degrees above 1023 and as an independent check.
 //   epilogue_kernel: best tracking, noise level, the adaptive step's jump,
 //     reweighting and systematic resampling of a step (one workgroup).
 //   icm_kernel / icm_apply_kernel: the cluster move on replica pairs;
@@ -1224,6 +1227,897 @@ __global__ __launch_bounds__(1024) void sweep_bytes_multi_kernel(const MultiRun 
 }
 
 // ---------------------------------------------------------------------------
+// Tile form of kernel 1: one workgroup holds W = 4, 8 or 16 replicas
+// in LDS for a whole step, as one record per node: a byte per replica (W = 4)
+// or a nibble (W = 8: one 32-bit word, W = 16: two), so an LDS read of four
+// bytes serves 8 replicas and at most 15 neighbours add up without a carry.
+//
+// What bounds a sweep is the chain of dependent steps of every dependency
+// level, closed by a barrier, with few waves to fill it: a wave alone issues
+// an instruction every 5 to 8 cycles. So a level's chain holds no draw (n =
+// 800, degree 10, R = 128: 159 us a launch of 10 sweeps with the byte form,
+// 113 with this one; degree 48, R = 1,024: 2,862 and 380):
+//
+//   draws    q = the largest half energy change m that the draw accepts
+//            (q = #{m >= 1 : draw < T[m]}). It depends on node, sweep, step
+//            and replica only, never on a spin, so the draws of a stretch
+//            (chunk) of the sweep are made while the chunk before it is
+//            decided, by the waves that a level leaves free, into the other
+//            half of an LDS buffer. The thresholds are looked up by the
+//            exponent and top four mantissa bits of the draw as a float: one
+//            entry {T, q} per bucket leaves one comparison.
+//   levels   one lane = one node (or 2^p lanes, each a part of the node's
+//            row, summed by DPP): v = neighbours with w_ij x_i x_j = -1, as
+//            XOR-and-add of the records; m = 2 v - d is compared with q for
+//            4 replicas in one subtraction. No table, no draw on the chain.
+//
+// Graphs of degree at most 8 with a few large levels (tori) have waves enough
+// and take the FUSE form, which draws in registers in the level's own pass
+// (100 x 100 torus, R = 16,384: 627 us a step of 5 sweeps with the byte
+// form, 583 with this one).
+//
+// Each wave walks a stream of items (item_word), dealt out by the host: nodes
+// of a level to decide, or 64 slots of the next chunk to draw, and where a
+// barrier or a change of buffer half follows. An item's block holds, row by
+// row, one uint4 per lane (coalesced): u16 {record, degree} and, where it is
+// read (FUSE, signed graphs), {node, sign bits or complement record}, then the
+// neighbours' record numbers, padded with the node's own record (x ^ x adds
+// nothing); a draw item's block is the nodes' numbers. Lanes past the item's
+// last node read the block's spare lane, a dummy node of degree 0. Every wave
+// has a dummy record of its own: a dummy lane reads its record twice, as its
+// own and as its neighbours', and no other wave may write in between.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kTabLo = 0x3F80;     // bucket entry of draw 1.0f: float bits >> 16, low 3 bits clear
+constexpr uint32_t kTabHi = 0x4F88;     // past the entry of 2^32
+constexpr uint32_t kTileLow = 1024;     // below: entry of draw 0, energies, counters, thresholds
+constexpr uint32_t kEdAt = 16, kCntAt = 144, kMultiAt = 160, kThrAt = 512;
+static_assert(kThrAt + 4 * 127 <= kTileLow, "threshold row");
+
+template <int W>
+struct TileRec {
+    static constexpr int words = W == 16 ? 2 : 1;
+    static constexpr int shift = W == 16 ? 3 : 2;               // record number -> LDS byte address
+    static constexpr uint32_t one = W == 4 ? 0x01010101u : 0x11111111u;
+    // Bit of replica b inside record word b >> 3.
+    static constexpr __host__ __device__ int bit(int b) { return W == 4 ? 8 * b : 8 * (b & 3) + 4 * ((b >> 2) & 1); }
+};
+
+// LDS address of record x. The draw buffer fills [kTileLow, kTabLo) and the
+// records follow the bucket table; without a buffer (FUSE) the records start
+// at kTileLow and step over the table.
+__host__ __device__ inline uint32_t tile_addr(int W, int fuse, uint32_t x)
+{
+    const uint32_t stride = W == 16 ? 8u : 4u;
+    if (!fuse) return kTabHi + x * stride;
+    const uint32_t at = kTileLow + x * stride;
+    return at < kTabLo ? at : at + (kTabHi - kTabLo);
+}
+
+int tile_record(int W, int fuse, int x) { return (int)(tile_addr(W, fuse, (uint32_t)x) >> (W == 16 ? 3 : 2)); }
+
+int item_word(int last, int slot, int rows, int lp, int kind)
+{
+    return (int)((uint32_t)last << 4 | (uint32_t)slot << 11 | (uint32_t)(rows - 1) << 23 | (uint32_t)lp << 25 |
+                 (uint32_t)kind << 28);
+}
+
+int sweep_tile_lds(int W, int comp, int n, int fuse)
+{
+    const uint32_t end = tile_addr(W, fuse, (uint32_t)((comp ? 2 * n : n) + kMaxThreads / 64));
+    return (int)((end > kTabHi ? end : kTabHi) + 15u & ~15u);
+}
+
+// Slots (multiple of 64) the draw buffer holds: 4 bytes per slot and 4
+// replicas, 8 with 16-bit levels.
+int tile_draw_slots(int W, int deg16)
+{
+    const int per = deg16 ? 2 * W : W;
+    return (int)(kTabLo - kTileLow) / per / 64 * 64;
+}
+
+__device__ __forceinline__ uint32_t lds_get(uint32_t at) { return *(lds_u32 *)(uintptr_t)at; }
+__device__ __forceinline__ void lds_set(uint32_t at, uint32_t v) { *(lds_u32 *)(uintptr_t)at = v; }
+
+// Fields of an item's second word (item_word).
+__device__ __forceinline__ uint32_t item_last16(uint32_t x) { return x & 0x7F0u; }
+__device__ __forceinline__ uint32_t item_slot(uint32_t x) { return (x >> 11) & 4095u; }
+__device__ __forceinline__ int item_rows(uint32_t x) { return (int)((x >> 23) & 3u) + 1; }
+__device__ __forceinline__ int item_lp(uint32_t x) { return (int)((x >> 25) & 7u); }
+constexpr uint32_t kItemKind = 3u << 28;
+
+// Record address of the entry in the low or high half of a block word: one
+// instruction each (a word-select shift).
+template <int SHIFT, bool HIGH>
+__device__ __forceinline__ uint32_t entry_addr(uint32_t w)
+{
+    uint32_t at;
+    if constexpr (HIGH)
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+            : "=v"(at) : "v"(SHIFT), "v"(w));
+    else
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
+            : "=v"(at) : "v"(SHIFT), "v"(w));
+    return at;
+}
+
+// c + (a ^ b), one instruction.
+__device__ __forceinline__ uint32_t xor_add(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t r;
+    asm("v_xad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// A lane's block of an item: up to 3 rows of 8 u16 (6 or, with the long
+// header, 4 entries, then 8 each).
+struct TileBlk {
+    uint4 r0, r1, r2;
+};
+
+// (m & a) | (~m & b) and (a << 1) + b, one instruction each (the compiler
+// takes them apart again).
+__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b)
+{
+    uint32_t r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(m), "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ uint32_t twice_plus(uint32_t a, uint32_t b)
+{
+    uint32_t r;
+    asm("v_lshl_add_u32 %0, %1, 1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+
+// Largest draw of bucket b (0 = draw 1, 512 = the draws that round to 2^32).
+// A draw's bucket is its value rounded to a float (nearest, ties to even), cut
+// to the exponent and 4 mantissa bits: the draws below a boundary B that lie
+// within half an ulp of it already round up to it.
+__host__ __device__ inline uint32_t bucket_last(int b)
+{
+    if (b >= 512) return 0xFFFFFFFFu;
+    const int e = (b + 1) >> 4, f = (b + 1) & 15;     // B = 2^e (1 + f/16)
+    // ceil(B) in integers: 2^e (16 + f) / 16.
+    const uint64_t s16 = (uint64_t)(16 + f) << e;
+    const uint64_t B = (s16 + 15) >> 4;
+    const int below = f == 0 ? e - 1 : e;             // binade of the draws just below B
+    const uint64_t half = below >= 24 ? 1ull << (below - 24) : 0ull;
+    return (uint32_t)(B - 1 - half);
+}
+
+// The table entry that holds draw d.
+__device__ __forceinline__ uint32_t draw_entry(uint32_t d)
+{
+    return (__float_as_uint((float)d) >> 16) & 0xFFF8u;
+}
+
+// #{m : T[m] > x} of a non-increasing row T[1..len] (index 0 = T[1]).
+template <typename Row>
+__device__ __forceinline__ int count_above(Row T, int len, uint32_t x)
+{
+    int lo = 0, hi = len;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (T[mid] > x) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// SG: 0 = all weights positive; 1 = negative edges read a complemented copy of
+// the neighbour's record (twice the records); 2 = sign bits in the block, the
+// record complemented on reading (two instructions per neighbour).
+// DEG: 0 = degrees up to 63; 1 = up to 127; 2 = 16-bit counters.
+// One workgroup's step: tile `blk` (replicas blk*W .. blk*W + W - 1) of a run
+// whose sweep launch has `nblk` tiles.
+template <int W, int SG, int DEG, bool FUSE>
+__device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__restrict__ items,
+                                           const int4 *__restrict__ streams, const uint4 *__restrict__ blocks,
+                                           const int blk, const int nblk, const bool prio)
+{
+    using TR = TileRec<W>;
+    constexpr bool D16 = DEG == 2;
+    constexpr int NR = TR::words;               // record words
+    constexpr int NQ = W / 4;                   // Philox calls per node
+    constexpr int ND = D16 ? W / 2 : W / 4;     // decision words
+    constexpr bool LONG = FUSE || SG != 0;      // block header of 4 u16, else 2
+    constexpr int E0 = LONG ? 4 : 6;            // entries of a block's first row
+    constexpr uint32_t ONE = TR::one;
+    constexpr uint32_t BIAS = D16 ? 0x7FFFu : 0x7Fu;
+    constexpr uint32_t BIASW = D16 ? 0x7FFF7FFFu : 0x7F7F7F7Fu;
+    static_assert(!D16 || W == 4, "16-bit counters take 4 replicas");
+    const int gk = a.adapt ? a.as_state[3] : a.k;     // grid point of this step
+    if (gk >= a.K) {
+        // A finished run (adaptive steps past the last grid point): carry the
+        // population over to the output buffer unchanged (the parent list is
+        // the identity then), each workgroup a slice.
+        const size_t words = (size_t)((a.R + 63) >> 6) * a.n;
+        const size_t per = (words + nblk - 1) / nblk;
+        const size_t w0 = (size_t)blk * per, w1 = w0 + per < words ? w0 + per : words;
+        for (size_t w = w0 + threadIdx.x; w < w1; w += blockDim.x) a.X[w] = a.Xin[w];
+        const int rper = (a.R + nblk - 1) / nblk;
+        const int e0 = blk * rper, e1 = e0 + rper < a.R ? e0 + rper : a.R;
+        for (int r = e0 + (int)threadIdx.x; r < e1; r += blockDim.x) a.E[r] = a.Ein[r];
+        return;
+    }
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int n = a.n;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nt = blockDim.x, nw = nt >> 6;
+    const int r0 = blk * W;
+    const int grp = r0 >> 6;
+    const int sub = (r0 & 63) / W;
+    int *Ed = reinterpret_cast<int *>(smem + kEdAt);                 // [2][16]
+    unsigned long long *cnt_s = reinterpret_cast<unsigned long long *>(smem + kCntAt);
+    int *multi_s = reinterpret_cast<int *>(smem + kMultiAt);
+    uint32_t *Trow = reinterpret_cast<uint32_t *>(smem + (D16 ? kTileLow : kThrAt));
+    const int dmax = a.dmax;
+
+    uint64_t *Xg = a.X + (size_t)grp * n;            // output words of this block's group
+    // The block's replica slots take the spins of their resampling parents
+    // (identity before the first resampling). Systematic resampling hands
+    // out slots in parent order, so the parents of a block normally sit in
+    // one or two 64-replica words: those are read once per node.
+    const bool ident = a.parent == nullptr;
+    int pr[W];
+    int gA = 1 << 30, gB = -1;
+#pragma unroll
+    for (int b = 0; b < W; ++b) {
+        const int r = r0 + b < a.R ? r0 + b : r0;
+        pr[b] = ident ? r : a.parent[r];
+        gA = (pr[b] >> 6) < gA ? (pr[b] >> 6) : gA;
+        gB = (pr[b] >> 6) > gB ? (pr[b] >> 6) : gB;
+    }
+    const bool two = gB - gA <= 1;
+    const uint64_t *XA = a.Xin + (size_t)gA * n, *XB = a.Xin + (size_t)gB * n;
+    const int level = a.as_state[0];
+    const uint32_t *trow = a.thr32 + ((size_t)gk * a.lmax1 + level) * (size_t)(dmax + 1);
+    for (int m = tid; m < dmax; m += nt) Trow[m] = trow[m];
+    // Accept-all row (exp(-beta * 2m) rounds to 1 for every uphill move).
+    const bool all = trow[dmax] != 0;
+    // Energies: lane r of every wave carries replica r0 + r.
+    const bool mine = lane < W && r0 + lane < a.R;
+    int e_r = 0;
+    if (mine) e_r = a.Ein[ident ? r0 + lane : a.parent[r0 + lane]];
+    int best = a.best_E[0];
+    unsigned long long cand = ~0ull;
+    if (tid < 32) Ed[tid] = 0;
+    if (tid < 2) cnt_s[tid] = 0;
+    if (tid == 2) *multi_s = 0;
+    const uint32_t dummy = tile_addr(W, FUSE, (uint32_t)((SG == 1 ? 2 * n : n) + wave));
+    if (lane < NR) lds_set(dummy + 4 * lane, 0u);
+    __syncthreads();
+    // Bucket table of the step's thresholds.
+    for (int b = tid - 1; b <= 512; b += nt) {
+        const uint32_t at = b < 0 ? 0u : kTabLo + 8u * (uint32_t)b;
+        uint32_t thr = 0, q = (uint32_t)dmax;
+        if (!all) {
+            const uint32_t last = b < 0 ? 0u : bucket_last(b);
+            q = (uint32_t)count_above(Trow, dmax, last);
+            if (b >= 0 && (int)q < dmax) {
+                thr = Trow[q];
+                // A second threshold inside the bucket: this step compares by search.
+                const uint32_t first = b == 0 ? 1u : bucket_last(b - 1) + 1u;
+                if ((int)q + 1 < dmax && Trow[q + 1] > first) *multi_s = 1;
+            }
+        }
+        *(lds_u2 *)(uintptr_t)at = u32x2{thr, q};
+    }
+
+    // Expand the block's spin bits into records, LB nodes per lane and pass
+    // (their loads in flight together). With resampling parents in two words,
+    // slot b's spin is one bit of one 32-bit half of those words, the same
+    // for every node: the half is picked by a uniform branch per slot, so a
+    // spin costs one bit extract.
+    {
+        constexpr int LB = 4;
+        int psel[W];
+#pragma unroll
+        for (int b = 0; b < W; ++b)
+            psel[b] = __builtin_amdgcn_readfirstlane(((pr[b] >> 6) == gA ? 0 : 2) + ((pr[b] & 63) >= 32 ? 1 : 0));
+        for (int base = 0; base < n; base += LB * nt) {
+            uint64_t va[LB], vb[LB];
+#pragma unroll
+            for (int u = 0; u < LB; ++u) {
+                const int i = base + u * nt + tid;
+                va[u] = i < n ? XA[i] : 0ull;
+                vb[u] = i < n && !ident && two ? XB[i] : 0ull;
+            }
+            Rec<NR> rc[LB];
+            auto put_field = [&](Rec<NR> &r, uint32_t v) {
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    r.v[q] = spread4(v >> (8 * q));
+                    if constexpr (W >= 8) r.v[q] |= spread4(v >> (8 * q + 4)) << 4;
+                }
+            };
+            if (ident) {
+#pragma unroll
+                for (int u = 0; u < LB; ++u) put_field(rc[u], (uint32_t)(va[u] >> (W * sub)) & ((1u << W) - 1u));
+            } else if (two) {
+#pragma unroll
+                for (int u = 0; u < LB; ++u)
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) rc[u].v[q] = 0u;
+#pragma unroll
+                for (int b = 0; b < W; ++b) {
+                    const uint32_t sh = (uint32_t)__builtin_amdgcn_readfirstlane(pr[b] & 31);
+                    const int q = b >> 3, bs = TR::bit(b);
+                    if (psel[b] == 0) {
+#pragma unroll
+                        for (int u = 0; u < LB; ++u) rc[u].v[q] |= (((uint32_t)va[u] >> sh) & 1u) << bs;
+                    } else if (psel[b] == 1) {
+#pragma unroll
+                        for (int u = 0; u < LB; ++u) rc[u].v[q] |= (((uint32_t)(va[u] >> 32) >> sh) & 1u) << bs;
+                    } else if (psel[b] == 2) {
+#pragma unroll
+                        for (int u = 0; u < LB; ++u) rc[u].v[q] |= (((uint32_t)vb[u] >> sh) & 1u) << bs;
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < LB; ++u) rc[u].v[q] |= (((uint32_t)(vb[u] >> 32) >> sh) & 1u) << bs;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < LB; ++u) {
+                    const int i = base + u * nt + tid;
+                    uint32_t v = 0;
+                    if (i < n) {
+#pragma unroll
+                        for (int b = 0; b < W; ++b)
+                            v |= (uint32_t)((a.Xin[(size_t)(pr[b] >> 6) * n + i] >> (pr[b] & 63)) & 1ull) << b;
+                    }
+                    put_field(rc[u], v);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < LB; ++u) {
+                const int i = base + u * nt + tid;
+                if (i >= n) break;
+                rec_store<NR>(tile_addr(W, FUSE, (uint32_t)i), rc[u]);
+                if constexpr (SG == 1) {
+                    Rec<NR> cc;
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) cc.v[q] = rc[u].v[q] ^ ONE;
+                    rec_store<NR>(tile_addr(W, FUSE, (uint32_t)(n + i)), cc);
+                }
+            }
+        }
+    }
+    // Top bits of the fields of real (non-padding) replicas, for the counters.
+    uint32_t real[ND];
+#pragma unroll
+    for (int q = 0; q < ND; ++q) {
+        uint32_t m = 0;
+        if constexpr (D16) {
+            if (r0 + q < a.R) m |= 0x8000u;
+            if (r0 + q + 2 < a.R) m |= 0x80000000u;
+        } else {
+            for (int b = 0; b < 4; ++b)
+                if (r0 + 4 * q + b < a.R) m |= 0x80u << (8 * b);
+        }
+        real[q] = m;
+    }
+    __syncthreads();
+    const bool multi = __builtin_amdgcn_readfirstlane(*multi_s) != 0;
+
+    const uint32_t k = (uint32_t)a.k;
+    const uint32_t rgrp0 = (uint32_t)(r0 >> 2) | (a.inst << 16);
+
+    // Levels q of the draws of one node, packed like the decision words.
+    auto draws = [&](uint32_t node, uint32_t s, uint32_t (&q)[ND]) {
+        uint32_t d[NQ][4];
+#pragma unroll
+        for (int g = 0; g < NQ; ++g) {
+            const U4 o = philox10(U4{node, s, k, rgrp0 + (uint32_t)g}, a.seed_lo, a.seed_hi);
+            d[g][0] = o.x; d[g][1] = o.y; d[g][2] = o.z; d[g][3] = o.w;
+        }
+        if (!multi) {
+#pragma unroll
+            for (int g = 0; g < NQ; ++g)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const u32x2 e = *(lds_u2 *)(uintptr_t)draw_entry(d[g][b]);
+                    d[g][b] = e.y + (d[g][b] < e.x ? 1u : 0u);
+                }
+        } else {
+#pragma unroll
+            for (int g = 0; g < NQ; ++g)
+#pragma unroll 1
+                for (int b = 0; b < 4; ++b) {
+                    const uint32_t x = b == 0 ? d[g][0] : b == 1 ? d[g][1] : b == 2 ? d[g][2] : d[g][3];
+                    const uint32_t c = (uint32_t)count_above(trow, dmax, x);
+                    d[g][0] = b == 0 ? c : d[g][0];
+                    d[g][1] = b == 1 ? c : d[g][1];
+                    d[g][2] = b == 2 ? c : d[g][2];
+                    d[g][3] = b == 3 ? c : d[g][3];
+                }
+        }
+#pragma unroll
+        for (int g = 0; g < NQ; ++g) {
+            if constexpr (D16) {
+                q[0] = d[g][0] | d[g][2] << 16;
+                q[1] = d[g][1] | d[g][3] << 16;
+            } else {
+                q[g] = d[g][0] | d[g][1] << 8 | d[g][2] << 16 | d[g][3] << 24;
+            }
+        }
+    };
+    auto q_at = [&](uint32_t at, uint32_t (&q)[ND]) {
+        if constexpr (ND == 1) {
+            q[0] = lds_get(at);
+        } else if constexpr (ND == 2) {
+            const u32x2 t = *(lds_u2 *)(uintptr_t)at;
+            q[0] = t.x; q[1] = t.y;
+        } else {
+            const u32x4 t = *(lds_u4 *)(uintptr_t)at;
+            q[0] = t.x; q[1] = t.y; q[2] = t.z; q[3] = t.w;
+        }
+    };
+    auto q_put = [&](uint32_t at, const uint32_t (&q)[ND]) {
+        if constexpr (ND == 1) lds_set(at, q[0]);
+        else if constexpr (ND == 2) *(lds_u2 *)(uintptr_t)at = u32x2{q[0], q[1]};
+        else *(lds_u4 *)(uintptr_t)at = u32x4{q[0], q[1], q[2], q[3]};
+    };
+    // Uphill counters and energy changes of this lane. acc holds, per decision
+    // word, the sums of bias + m over accepted flips (bias alone where none
+    // was accepted) in 16-bit halves; `items_done` counts the biases.
+    constexpr int NA = D16 ? W : 2 * ND;
+    uint32_t acc[NA];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) acc[q] = 0;
+    int items_done = 0;
+    unsigned int att_c = 0, acc_c = 0;
+    int last0 = 0, last1 = 0;          // energy sums already taken from Ed
+
+    // The wave's energy changes into the workgroup's sums of sweep parity p:
+    // four lanes add their four words (64 items fill a 16-bit half then),
+    // lane l goes on with word l mod 4, rows of 16 lanes add up by DPP.
+    auto flush = [&](int p) {
+        if (items_done == 0) return;
+        const int bias = (int)BIAS * 16 * items_done;
+        constexpr int L = NA < 4 ? NA : 4;              // lanes that share out the words
+#pragma unroll
+        for (int base = 0; base < NA; base += 4) {
+            uint32_t w[L];
+#pragma unroll
+            for (int t = 0; t < L; ++t) {
+                w[t] = acc[base + t];
+                w[t] += dpp<0xB1>(w[t]);                         // quad_perm 1,0,3,2
+                if constexpr (L == 4) w[t] += dpp<0x4E>(w[t]);   // quad_perm 2,3,0,1
+                acc[base + t] = 0;
+            }
+            const int l = lane & (L - 1);
+            uint32_t v = w[0];
+#pragma unroll
+            for (int t = 1; t < L; ++t) v = l == t ? w[t] : v;
+            int e0 = D16 ? (int)v : (int)(v & 0xFFFFu), e1 = (int)(v >> 16);
+            auto row = [](int x) {
+                if constexpr (L == 2) x += (int)dpp<0x122>((uint32_t)x);     // row_ror:2
+                x += (int)dpp<0x124>((uint32_t)x);                           // row_ror:4
+                return x + (int)dpp<0x128>((uint32_t)x);                     // row_ror:8
+            };
+            e0 = 2 * (row(e0) - bias);
+            if constexpr (!D16) e1 = 2 * (row(e1) - bias);
+            // Word t of a group of four words: replicas 4 (t / 2) + (t & 1)
+            // and two after it (16-bit counters: replica t).
+            const int r = 2 * base + (D16 ? l : 4 * (l >> 1) + (l & 1));
+            if ((lane & 15) < L) {
+                atomicAdd(&Ed[16 * p + r], e0);
+                if constexpr (!D16) atomicAdd(&Ed[16 * p + r + 2], e1);
+            }
+        }
+        items_done = 0;
+    };
+
+    // Decide one item: the nodes of a level that this wave takes together.
+    auto decide = [&](const TileBlk &c, const uint32_t h, uint32_t s, uint32_t qbuf) {
+        const uint32_t own = entry_addr<TR::shift, false>(c.r0.x);
+        uint32_t d = c.r0.x >> 16;
+        const int rows = FUSE ? 1 : item_rows(h), lp = item_lp(h);
+        const Rec<NR> X = rec_load<NR>(own);
+        uint32_t q[ND];
+        if constexpr (!FUSE) {
+            const uint32_t me = lp == 0 ? (uint32_t)lane : (uint32_t)lane >> lp;
+            q_at(qbuf + item_slot(h) * (4u * ND) + me * (4u * ND), q);
+        }
+        auto lo = [&](uint32_t w) { return rec_load<NR>(entry_addr<TR::shift, false>(w)); };
+        auto hi = [&](uint32_t w) { return rec_load<NR>(entry_addr<TR::shift, true>(w)); };
+        // Sum of (neighbour ^ own) over a row's entries, the neighbour
+        // complemented for a negative edge.
+        auto add = [&](Rec<NR> &C, const Rec<NR> &y, int j) {
+            if constexpr (SG == 2) {
+                const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)c.r0.y, 16 + j, 1);
+#pragma unroll
+                for (int t = 0; t < NR; ++t)
+                    C.v[t] = xor_add((uint32_t)__builtin_amdgcn_bitop3_b32(y.v[t], m, ONE, 0x78), X.v[t], C.v[t]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < NR; ++t) C.v[t] = xor_add(y.v[t], X.v[t], C.v[t]);
+            }
+        };
+        uint32_t V[ND];
+        auto widen = [&](const Rec<NR> &C, bool first) {
+            if constexpr (D16) {
+                const uint32_t v0 = C.v[0] & 0x00FF00FFu, v1 = (C.v[0] >> 8) & 0x00FF00FFu;
+                V[0] = first ? v0 : V[0] + v0;
+                V[1] = first ? v1 : V[1] + v1;
+            } else if constexpr (W == 4) {
+                V[0] = first ? C.v[0] : V[0] + C.v[0];
+            } else {
+#pragma unroll
+                for (int t = 0; t < NR; ++t) {
+                    const uint32_t v0 = C.v[t] & 0x0F0F0F0Fu, v1 = (C.v[t] >> 4) & 0x0F0F0F0Fu;
+                    V[2 * t] = first ? v0 : V[2 * t] + v0;
+                    V[2 * t + 1] = first ? v1 : V[2 * t + 1] + v1;
+                }
+            }
+        };
+        Rec<NR> y[E0];
+        if constexpr (!LONG) {
+            y[4] = lo(c.r0.y);
+            y[5] = hi(c.r0.y);
+        }
+        y[0] = lo(c.r0.z); y[1] = hi(c.r0.z); y[2] = lo(c.r0.w); y[3] = hi(c.r0.w);
+        if constexpr (FUSE) {
+            // The reads above are in flight while the draws are computed.
+            __builtin_amdgcn_sched_barrier(0);
+            draws(c.r0.y & 0xFFFFu, s, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // The eight (half: four) records of a row.
+        auto row = [&](const uint4 &r, Rec<NR> (&z)[8], bool half) {
+            z[0] = lo(r.x); z[1] = hi(r.x); z[2] = lo(r.y); z[3] = hi(r.y);
+            if (!half) {
+                z[4] = lo(r.z); z[5] = hi(r.z); z[6] = lo(r.w); z[7] = hi(r.w);
+            }
+        };
+        // Two sums in turn, so that an addition need not wait for the last.
+        Rec<NR> Ca, Cb;
+        auto zero = [&]() {
+#pragma unroll
+            for (int t = 0; t < NR; ++t) Ca.v[t] = Cb.v[t] = 0;
+        };
+        auto both = [&]() {
+#pragma unroll
+            for (int t = 0; t < NR; ++t) Ca.v[t] += Cb.v[t];
+        };
+        auto add_y = [&]() {
+            zero();
+#pragma unroll
+            for (int t = 0; t < E0; ++t) add(t & 1 ? Cb : Ca, y[t], t);
+        };
+        auto add_row = [&](const Rec<NR> (&z)[8], int j, bool half) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if (!half || t < 4) add(t & 1 ? Cb : Ca, z[t], j + t);
+        };
+        // All records of the item are requested before the first is added.
+        if (rows == 1) {
+            __builtin_amdgcn_sched_barrier(0);
+            add_y();
+            both();
+            widen(Ca, true);
+        } else if (rows == 2) {
+            Rec<NR> z[8];
+            row(c.r1, z, false);
+            __builtin_amdgcn_sched_barrier(0);
+            add_y();
+            add_row(z, E0, false);
+            both();
+            widen(Ca, true);
+        } else {
+            Rec<NR> z[8], u[8];
+            row(c.r1, z, false);
+            row(c.r2, u, SG == 2);          // 16 sign bits: the row's second half is padding
+            __builtin_amdgcn_sched_barrier(0);
+            add_y();
+            add_row(z, E0, false);
+            both();
+            widen(Ca, true);
+            zero();
+            add_row(u, E0 + 8, SG == 2);
+            both();
+            widen(Ca, false);
+        }
+        uint32_t to = own;
+        if (lp != 0) {
+            // 2^lp lanes share the node: sum their parts; the first lane
+            // decides, the others stand for dummy nodes.
+#pragma unroll
+            for (int t = 0; t < ND; ++t) V[t] += dpp<0xB1>(V[t]);            // quad_perm 1,0,3,2
+            if (lp > 1) {
+#pragma unroll
+                for (int t = 0; t < ND; ++t) V[t] += dpp<0x4E>(V[t]);        // quad_perm 2,3,0,1
+                if (lp > 2) {
+#pragma unroll
+                    for (int t = 0; t < ND; ++t) V[t] += dpp<0x141>(V[t]);   // row_half_mirror
+                    if (lp > 3) {
+#pragma unroll
+                        for (int t = 0; t < ND; ++t) {
+                            V[t] += dpp<0x140>(V[t]);                        // row_mirror
+                            if constexpr (D16) {
+                                if (lp > 4) V[t] += __shfl_xor(V[t], 16, 64);
+                                if (lp > 5) V[t] += __shfl_xor(V[t], 32, 64);
+                            }
+                        }
+                    }
+                }
+            }
+            const bool lead = (lane & ((1 << lp) - 1)) == 0;
+#pragma unroll
+            for (int t = 0; t < ND; ++t) V[t] = lead ? V[t] : 0u;
+            d = lead ? d : 0u;
+            to = lead ? own : dummy;
+        }
+        const uint32_t Dm = D16 ? d | d << 16 : __builtin_amdgcn_perm(0u, d, 0u);
+        const uint32_t c1 = BIASW - Dm;
+        uint32_t rj[ND];
+#pragma unroll
+        for (int t = 0; t < ND; ++t) {
+            const uint32_t w = twice_plus(V[t], c1);    // bias + m, m = 2 v - d: top bit = uphill
+            // Top bit of r: m > q, the flip is rejected.
+            uint32_t r;
+            if constexpr (DEG == 1) r = ((w | 0x80808080u) - q[t]) & w;
+            else r = w - q[t];
+            rj[t] = r;
+            att_c += __builtin_popcount(w & real[t]);
+            acc_c += __builtin_popcount(w & ~r & real[t]);
+            if constexpr (D16) {
+                const uint32_t z = bit_select(__builtin_amdgcn_perm(0u, r, 0x09090808u), BIASW, w);
+                acc[t] += z & 0xFFFFu;
+                acc[t + 2] += z >> 16;
+            } else {
+                const uint32_t z = bit_select(__builtin_amdgcn_perm(r << 8, r, 0x090B080Au), BIASW, w);
+                acc[2 * t] += z & 0x00FF00FFu;
+                acc[2 * t + 1] += __builtin_amdgcn_perm(0u, z, 0x0C030C01u);
+            }
+        }
+        Rec<NR> Xn;
+        if constexpr (D16) {
+            const uint32_t f = bit_select(0x00FF00FFu, rj[0] >> 15, rj[1] >> 7);
+            Xn.v[0] = (uint32_t)__builtin_amdgcn_bitop3_b32(X.v[0], f, ONE, 0xD2);
+        } else if constexpr (W == 4) {
+            Xn.v[0] = (uint32_t)__builtin_amdgcn_bitop3_b32(X.v[0], rj[0] >> 7, ONE, 0xD2);
+        } else {
+#pragma unroll
+            for (int t = 0; t < NR; ++t) {
+                const uint32_t f = bit_select(0x0F0F0F0Fu, rj[2 * t] >> 7, rj[2 * t + 1] >> 3);
+                Xn.v[t] = (uint32_t)__builtin_amdgcn_bitop3_b32(X.v[t], f, ONE, 0xD2);   // x ^ (~f & one)
+            }
+        }
+        rec_store<NR>(to, Xn);
+        if constexpr (SG == 1) {
+            const uint32_t comp = lp != 0 && to == dummy ? dummy : entry_addr<TR::shift, true>(c.r0.y);
+            Rec<NR> Xc;
+#pragma unroll
+            for (int t = 0; t < NR; ++t) Xc.v[t] = Xn.v[t] ^ ONE;
+            rec_store<NR>(comp, Xc);
+        }
+        if (++items_done == 64) flush((int)(s & 1u));
+    };
+    // Draw for 64 slots from `slot` on (padding slots draw for node 0).
+    auto produce = [&](uint32_t node, uint32_t slot, uint32_t s, uint32_t qbuf) {
+        uint32_t q[ND];
+        draws(node, s, q);
+        q_put(qbuf + (slot + (uint32_t)lane) * (4u * ND), q);
+    };
+
+    // The wave's item stream: while an item is worked on, the next item's
+    // block and the header of the third item ahead are on their way. Items go
+    // in pairs with the two block buffers' roles swapped (the host pads the
+    // sweep to an even count), so no registers are copied. Every step issues
+    // the same vector loads -- rows an item does not have are read from what
+    // follows its block and ignored -- so the wait for a block counts the
+    // loads behind it and leaves them in flight; headers come through vector
+    // loads too, because a scalar load would share the LDS counter and every
+    // wait for a record would wait for it.
+    constexpr int ROWS = FUSE ? 1 : 3;
+    TileBlk bA, bB;
+    const __amdgpu_buffer_rsrc_t brs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(blocks), 0, 0x7FFFFFF0, 0x00027000);
+    const int4 sw = streams[wave];                  // {first item, items, draw block, draw items}
+    const unsigned char *its = reinterpret_cast<const unsigned char *>(items + sw.x);
+    uint32_t lane16 = (uint32_t)lane * 16u;
+    uint32_t hat;                                   // byte offset of the next header, the same in every lane
+    asm("v_mov_b32 %0, 0" : "=v"(hat));             // (the compiler takes it for a lane's own)
+    auto head = [&]() {
+        const int2 v = *reinterpret_cast<const int2 *>(its + hat);
+        hat += 8u;
+        return v;
+    };
+    auto uni = [](const int2 &v) {
+        return int2{__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y)};
+    };
+    auto fetch = [&](TileBlk &b, const int2 &h) {
+        const uint32_t last = item_last16((uint32_t)h.y);
+        const uint32_t off = lane16 < last ? lane16 : last;
+        const int step = (int)last + 16;
+        auto get = [&](int soff) {
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(brs, (int)off, soff, 0);
+            return uint4{v.x, v.y, v.z, v.w};
+        };
+        b.r0 = get(h.x);
+        if constexpr (ROWS > 1) {
+            b.r1 = get(h.x + step);
+            b.r2 = get(h.x + step + step);
+        }
+    };
+    // Halves of the draw buffer: decided from qa, drawn into qa + qx.
+    uint32_t qa = kTileLow;
+    int qx = a.draw_half;
+    if constexpr (!FUSE) {
+        // The first chunk of the step.
+        for (int t = wave; t < sw.w; t += nw) {
+            const uint4 v = blocks[(size_t)sw.z + 64 * t + lane];
+            produce(v.x, 64u * (uint32_t)t, 0u, qa);
+        }
+    }
+    __syncthreads();
+    int2 h0 = uni(head()), h1 = uni(head());
+    int2 hv = head();
+    fetch(bA, h0);
+    auto step = [&](TileBlk &cur, TileBlk &nxt, uint32_t s) {
+        const int2 h3 = head();
+        fetch(nxt, h1);
+        const uint32_t x = (uint32_t)h0.y;
+        const uint32_t kind = x & kItemKind;
+        if (kind == (1u << 28)) {
+            decide(cur, x, s, qa);
+        } else if (!FUSE && kind != 0u) {
+            // 2: of this sweep, 3: of the next (none after the last).
+            const uint32_t s2 = s + (kind == kItemKind ? 1u : 0u);
+            if (s2 < (uint32_t)a.S) produce(cur.r0.x, item_slot(x), s2, qa + (uint32_t)qx);
+        }
+        if (x & (1u << 30)) __syncthreads();
+        if (!FUSE && (int)x < 0) {                  // the next chunk: change halves
+            qa += (uint32_t)qx;
+            qx = -qx;
+        }
+        h0 = h1;
+        h1 = uni(hv);
+        hv = h3;
+    };
+    // After the energy changes of sweep s are summed: energies, and the
+    // block's best candidate (lowest energy, then lowest replica; strict
+    // improvement only), the same in every wave; all take part in the
+    // snapshot of an improving replica. Returns whether one was taken.
+    auto sweep_end = [&](int s) {
+        const int p = s & 1;
+        const int now = Ed[16 * p + (lane & 15)];
+        const int was = p ? last1 : last0;
+        if (p) last1 = now;
+        else last0 = now;
+        e_r += now - was;
+        int key = mine ? e_r : 0x7FFFFFFF;
+        auto mn = [](int x, int y) { return x < y ? x : y; };
+        key = mn(key, (int)dpp<0x121>((uint32_t)key));       // row_ror:1, 2, 4, 8
+        key = mn(key, (int)dpp<0x122>((uint32_t)key));
+        key = mn(key, (int)dpp<0x124>((uint32_t)key));
+        key = mn(key, (int)dpp<0x128>((uint32_t)key));
+        const int low = __builtin_amdgcn_readfirstlane(key);
+        if (low >= best) return false;
+        best = low;
+        const int arg = (int)__builtin_ctzll(__ballot(mine && e_r == low));
+        cand = ((unsigned long long)((uint32_t)low ^ 0x80000000u) << 32) | ((unsigned long long)s << 15) |
+               (unsigned long long)(r0 + arg);
+        uint32_t *dst = a.snap + (size_t)blk * a.nw32;
+        const int bit = W == 4 ? 8 * arg : 8 * (arg & 3) + 4 * ((arg >> 2) & 1);
+        const uint32_t wofs = W == 16 ? 4u * (uint32_t)(arg >> 3) : 0u;
+        for (int i0 = 64 * wave; i0 < n; i0 += 64 * nw) {
+            const int i = i0 + lane;
+            const uint32_t x = i < n ? lds_get(tile_addr(W, FUSE, (uint32_t)i) + wofs) : 0u;
+            const unsigned long long m = __ballot((x >> bit) & 1u);
+            const int w = (i0 >> 5) + lane;
+            if (lane < 2 && w < a.nw32) dst[w] = lane ? (uint32_t)(m >> 32) : (uint32_t)m;
+        }
+        return true;
+    };
+    // Issue priority for sweep s (scheduling only): see build_plan.
+    auto prio_turn = [&](int s) {
+        if (!prio) return;
+        // Sweeps in which the second workgroup on a compute unit (slot 1,
+        // TG_ID of the HW_ID register) takes the higher issue priority: bits
+        // of s mod 10.
+        const uint32_t slot = (__builtin_amdgcn_s_getreg((31 << 11) | 4) >> 16) & 15u;
+        if (slot == 1 && ((0x2B5u >> (s % 10)) & 1u)) __builtin_amdgcn_s_setprio(2);
+        else __builtin_amdgcn_s_setprio(0);
+    };
+
+    for (int s = 0; s < a.S; ++s) {
+        prio_turn(s);
+        for (int i = 0; i < sw.y; i += 2) {
+            step(bA, bB, (uint32_t)s);
+            step(bB, bA, (uint32_t)s);
+        }
+        hat -= 8u * (uint32_t)sw.y;                 // (the stream's end repeats its first items)
+        flush(s & 1);
+        __syncthreads();
+        if (sweep_end(s)) __syncthreads();          // the next sweep rewrites records
+    }
+
+    auto field = [&](int i) {
+        const Rec<NR> rc = rec_load<NR>(tile_addr(W, FUSE, (uint32_t)i));
+        uint32_t v = 0;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) {
+            v |= gather4(rc.v[q]) << (8 * q);
+            if constexpr (W >= 8) v |= gather4(rc.v[q] >> 4) << (8 * q + 4);
+        }
+        return v;
+    };
+    if constexpr (W >= 8) {
+        for (int i = tid; i < n; i += nt) {
+            const uint32_t v = field(i);
+            if constexpr (W == 16) reinterpret_cast<uint16_t *>(Xg + i)[sub] = (uint16_t)v;
+            else reinterpret_cast<uint8_t *>(Xg + i)[sub] = (uint8_t)v;
+        }
+    } else {
+        // 4-bit fields share a byte with the neighbouring block: flip the
+        // changed bits atomically. Only this block writes these 4 bits during
+        // the launch, so the words can be read first, 8 per lane in flight.
+        const int sh = 4 * (sub & 7);
+        for (int base = 0; base < n; base += 8 * nt) {
+            uint32_t old[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = base + u * nt + tid;
+                old[u] = i < n ? reinterpret_cast<const unsigned int *>(Xg + i)[sub >> 3] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = base + u * nt + tid;
+                if (i >= n) break;
+                const unsigned delta = (((unsigned)field(i) ^ (old[u] >> sh)) & 0xFu) << sh;
+                if (delta) atomicXor(reinterpret_cast<unsigned int *>(Xg + i) + (sub >> 3), delta);
+            }
+        }
+    }
+    if (wave == 0 && mine) a.E[r0 + lane] = e_r;
+    // Uphill counters: wave sums gathered in LDS, one global atomic per
+    // workgroup (not per wave) on the two step-wide counters.
+    const long long at = wave_sum_ll((long long)att_c), ac = wave_sum_ll((long long)acc_c);
+    if (lane == 0) {
+        if (at) atomicAdd(&cnt_s[0], (unsigned long long)at);
+        if (ac) atomicAdd(&cnt_s[1], (unsigned long long)ac);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        if (cnt_s[0]) atomicAdd(&a.counters[0], cnt_s[0]);
+        if (cnt_s[1]) atomicAdd(&a.counters[1], cnt_s[1]);
+        a.cand[blk] = cand;
+    }
+}
+
+template <int W, int SG, int DEG, bool FUSE, bool PRIO>
+__global__ __launch_bounds__(1024) void sweep_tile_kernel(SweepArgs a, const int2 *__restrict__ items,
+                                                          const int4 *__restrict__ streams,
+                                                          const uint4 *__restrict__ blocks)
+{
+    // Workgroups are dispatched round-robin over the 8 XCDs. For 8- and
+    // 16-replica tiles (plain byte stores) each XCD takes a contiguous range
+    // of tiles, so tiles sharing a 64-replica word share an L2; 4-replica
+    // tiles keep the plain order (their nibble stores are atomic XORs, which
+    // would then contend within one XCD).
+    const int nb = gridDim.x;
+    const int blk = [nb] {
+        const int b = blockIdx.x;
+        if constexpr (W < 8) return b;
+        const int x = b & 7, q = nb >> 3, rem = nb & 7;
+        return x * q + (x < rem ? x : rem) + (b >> 3);
+    }();
+    sweep_tile<W, SG, DEG, FUSE>(a, items, streams, blocks, blk, nb, PRIO);
+}
+
+// ---------------------------------------------------------------------------
 // Step epilogue (one workgroup): best-candidate reduction, population best
 // check, noise-level update, statistics, reweighting and systematic
 // resampling counts -> parent list.
@@ -2141,6 +3035,64 @@ int launch_sweep_bytes(int W, int sgn, int threads, int nblk, const SweepArgs &a
     case 16: return launch_bytes_w<16>(sgn, threads, nblk, a, stream);
     default:
         snprintf(g_err, sizeof g_err, "unsupported byte-tile width %d", W);
+        return -1;
+    }
+}
+
+template <int W, int SG, int DEG, bool FUSE>
+static int launch_tile_t(int threads, int nblk, int lds, const SweepArgs &a, void *stream)
+{
+    // The issue-priority turns are compiled only into 8-replica tiles.
+    constexpr bool kHasPrio = W == 8 && SG == 0 && DEG == 0 && !FUSE;
+    const bool prio = kHasPrio && a.prio_mode == 1;
+    const void *fn = prio ? reinterpret_cast<const void *>(&sweep_tile_kernel<W, SG, DEG, FUSE, kHasPrio>)
+                          : reinterpret_cast<const void *>(&sweep_tile_kernel<W, SG, DEG, FUSE, false>);
+    static int configured[kMaxDevices] = {}, configured_p[kMaxDevices] = {};
+    if (allow_lds(fn, prio ? configured_p : configured, lds, "hipFuncSetAttribute(sweep_tile)")) return -1;
+    if (prio)
+        hipLaunchKernelGGL((sweep_tile_kernel<W, SG, DEG, FUSE, kHasPrio>), dim3(nblk), dim3(threads), lds,
+                           (hipStream_t)stream, a, a.items, a.streams, a.blocks);
+    else
+        hipLaunchKernelGGL((sweep_tile_kernel<W, SG, DEG, FUSE, false>), dim3(nblk), dim3(threads), lds,
+                           (hipStream_t)stream, a, a.items, a.streams, a.blocks);
+    return check("sweep_tile_kernel");
+}
+
+template <int W>
+static int launch_tile_w(int sg, int deg, int fuse, int threads, int nblk, int lds, const SweepArgs &a,
+                         void *stream)
+{
+    if (deg == 0 && fuse) {
+        if constexpr (W <= 8) {
+            if (sg == 2) return launch_tile_t<W, 2, 0, true>(threads, nblk, lds, a, stream);
+            if (sg == 0) return launch_tile_t<W, 0, 0, true>(threads, nblk, lds, a, stream);
+        }
+    } else if (deg == 0) {
+        if (sg == 2) return launch_tile_t<W, 2, 0, false>(threads, nblk, lds, a, stream);
+        if (sg == 1) return launch_tile_t<W, 1, 0, false>(threads, nblk, lds, a, stream);
+        return launch_tile_t<W, 0, 0, false>(threads, nblk, lds, a, stream);
+    } else if (deg == 1 && !fuse) {
+        if (sg == 2) return launch_tile_t<W, 2, 1, false>(threads, nblk, lds, a, stream);
+        if (sg == 0) return launch_tile_t<W, 0, 1, false>(threads, nblk, lds, a, stream);
+    } else if (deg == 2 && !fuse) {
+        if constexpr (W == 4) {
+            if (sg == 2) return launch_tile_t<W, 2, 2, false>(threads, nblk, lds, a, stream);
+            if (sg == 0) return launch_tile_t<W, 0, 2, false>(threads, nblk, lds, a, stream);
+        }
+    }
+    snprintf(g_err, sizeof g_err, "no tile kernel for W=%d records %d degrees %d fuse %d", W, sg, deg, fuse);
+    return -1;
+}
+
+int launch_sweep_tile(int W, int sg, int deg, int fuse, int threads, int nblk, int lds, const SweepArgs &a,
+                      void *stream)
+{
+    switch (W) {
+    case 4: return launch_tile_w<4>(sg, deg, fuse, threads, nblk, lds, a, stream);
+    case 8: return launch_tile_w<8>(sg, deg, fuse, threads, nblk, lds, a, stream);
+    case 16: return launch_tile_w<16>(sg, deg, fuse, threads, nblk, lds, a, stream);
+    default:
+        snprintf(g_err, sizeof g_err, "unsupported tile width %d", W);
         return -1;
     }
 }
