@@ -230,7 +230,7 @@ pa_status pa_host::check_schedule(const pa_solver *s, const pa_schedule *sch, in
 // neighbours visited before i (0 if none). Nodes of one level are pairwise
 // non-adjacent, and visiting levels in increasing order reproduces the
 // sequential sweep exactly, since each attempt only reads its neighbours.
-static void build_levels(const pa_solver *s, const int32_t *order, Plan &p)
+void pa_host::build_levels(const pa_solver *s, const int32_t *order, Plan &p)
 {
     const int n = s->n;
     std::vector<int> pos(n), lvl(n, 0);
@@ -703,6 +703,29 @@ static size_t tile_bytes(const pa_solver *s, const Plan &p)
            align_up(sizeof(int) * p.streams.size()) + tail_bytes(s, p, sizeof(uint32_t));
 }
 
+// A compute unit holds 16 waves of the tile kernel; a workgroup takes its share
+// of them (n = 4,000, degree 12, R = 16,384, four resident: 873 with 256
+// threads, 1,145 with 512; R = 1,024, one resident, 100 x 100 torus: 125 with
+// 1,024, 140 with 512). Small levels have no use for more than 512 threads (n =
+// 800: 123 with either), levels of thousands of nodes none for less (the torus
+// at R = 8,192: 625 with 512, 677 with 256).
+int pa_host::tile_threads(int need, int lds, int max_lds, long long per_level)
+{
+    const int res = std::min(need, max_lds / lds);
+    return res <= 1 ? (per_level >= 100 ? 1024 : 512) : res == 2 || per_level >= 1000 ? 512 : 256;
+}
+
+// As in take_tile_form, for launches that many runs share: the byte form keeps
+// rows that its registers hold on levels of more than 350 nodes, unless its
+// records leave a compute unit one workgroup where the tile form's leave two.
+bool pa_host::shared_tile_form(const pa_solver *s, int n_levels, int max_lds, int *fuse)
+{
+    if (s->has_neg && s->n + 256 > 0x7FFF) return false;
+    *fuse = fuse_draws(s->n, n_levels, s->dmax);
+    return *fuse || s->dmax > kBytesRegDegree || s->n / n_levels <= 350 ||
+           (2 * pa::sweep_bytes_lds(8, 0, s->n, s->dmax) > max_lds && 2 * pa::sweep_tile_lds(8, 0, s->n, 0) <= max_lds);
+}
+
 // Whether a run takes the tile form, and its shape then; p comes with the
 // general form's choice and the levels. All figures: one step of 10 sweeps on
 // MI355X, microseconds.
@@ -741,17 +764,7 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
     }
     if (lds(p.W) > max_lds) return false;
     p.nblk = (p.R + p.W - 1) / p.W;
-    if (sch->wg_threads == 0) {
-        // A compute unit holds 16 of this kernel's waves; a workgroup takes
-        // its share of them (n = 4,000, degree 12, R = 16,384, four resident:
-        // 873 with 256 threads, 1,145 with 512; R = 1,024, one resident, 100 x
-        // 100 torus: 125 with 1,024, 140 with 512). Small levels have no use
-        // for more than 512 threads (n = 800: 123 with either), levels of
-        // thousands of nodes none for less (the torus at R = 8,192: 625 with
-        // 512, 677 with 256).
-        const int need = (p.nblk + cus - 1) / cus, res = std::min(need, max_lds / lds(p.W));
-        p.threads = res == 1 ? (per_level >= 100 ? 1024 : 512) : res == 2 || per_level >= 1000 ? 512 : 256;
-    }
+    if (sch->wg_threads == 0) p.threads = tile_threads((p.nblk + cus - 1) / cus, lds(p.W), max_lds, per_level);
     // Form. The tile form shortens the chain of a level, and long rows spread
     // over lanes (n = 800, R = 1,024: 187 -> 131 at degree 12, 2,870 -> 380
     // at 48, where rows run past the general form's registers; degree 200 on
@@ -867,17 +880,41 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
             (force->bsg == 2 && n + pa::kBytesRecBase / 4 > 0x7FFF))
             return fail(PA_EINVAL, "shared launch record mode %d does not suit this graph", force->bsg);
         p.bsg = force->bsg;
-        if (pa::sweep_bytes_lds(force->W, 0, n, s->dmax) > max_lds)
+        if (force->lds(n, s->dmax) > max_lds)
             return fail(PA_ERANGE, "graph of %d nodes does not fit LDS with %d replicas per workgroup", n,
                         force->W);
-        if (force->direct && pa::kBytesRecBase + (size_t)(n + 1) * force->W > 0xFFFF)
+        if (!force->ahead && force->direct && pa::kBytesRecBase + (size_t)(n + 1) * force->W > 0xFFFF)
             return fail(PA_ERANGE, "graph of %d nodes too large for offset entries at tile %d", n, force->W);
+        if (force->ahead && (force->deg < degree_class(s->dmax) ||
+                             (force->fuse && (force->deg != 0 || s->dmax > 8 || force->W > 8))))
+            return fail(PA_EINVAL, "shared launch counters %d do not suit this graph", force->deg);
         p.kind = 1;
         p.W = force->W;
         p.threads = force->threads;
         p.nblk = (R + p.W - 1) / p.W;
         build_levels(s, sch->order, p);
-        build_blocks(s, p, force->direct);
+        if (force->ahead) {
+            p.ahead = 1;
+            p.deg = force->deg;
+            p.fuse = force->fuse;
+            build_tile_plan(s, p);
+            if (force->byte_threads != 0) {
+                Plan q;
+                q.kind = 1;
+                q.K = p.K;
+                q.lmax1 = p.lmax1;
+                q.nw32 = p.nw32;
+                q.W = force->byte_W;
+                q.threads = force->byte_threads;
+                q.nblk = (R + q.W - 1) / q.W;
+                q.n_levels = p.n_levels;
+                q.level_off = p.level_off;
+                const size_t general = general_bytes(s, q), own = tile_bytes(s, p);
+                p.pad = general > own ? general - own : 0;
+            }
+        } else {
+            build_blocks(s, p, force->direct);
+        }
     } else if (req != 2 && bytes_ok) {
         W = tile;
         // A requested tile takes the thread count of the automatic plan for
@@ -1119,7 +1156,7 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
     // What a run needs is no less with one form than with the other, so a
     // workspace that was too small stays so.
     L.total = o + p.pad;
-    if (p.ahead && L.total > room) {
+    if (p.ahead && !force && L.total > room) {
         p = Plan();
         return build_plan(s, sch, R, p, tables, nullptr, 0);
     }

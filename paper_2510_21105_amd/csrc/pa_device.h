@@ -171,11 +171,14 @@ int item_word(int last, int slot, int rows, int lp, int kind);
 int launch_sweep_tile(int W, int sg, int deg, int fuse, int threads, int nblk, int lds, const SweepArgs &a,
                       void *stream);
 int launch_epilogue(const EpiArgs &a, void *stream);
-// Multi-run launches: `blocks` workgroups over the work list {run, tile}
-// (sgn 0 unsigned records, 2 sign bits; `lds` the largest run's sweep LDS),
-// and one epilogue workgroup per run (max_R: the largest population).
-int launch_sweep_multi(int W, int sgn, bool direct, int threads, int blocks, int lds, const MultiRun *runs,
-                       const int2 *work, int k, void *stream);
+// Multi-run launches: `blocks` workgroups over the work list {run, tile}, and
+// one epilogue workgroup per run (max_R: the largest population).
+struct MultiShape {
+    int W, sgn;                 // sgn: 0 unsigned records, 2 sign bits
+    int ahead, direct, deg, fuse;   // the tile form with counters deg, or the byte form's entries
+    int threads, blocks, lds;   // lds: of the largest run's sweep
+};
+int launch_sweep_multi(const MultiShape &sh, const MultiRun *runs, const int2 *work, int k, void *stream);
 int launch_epilogue_multi(int runs_count, int max_R, const MultiRun *runs, int k, void *stream);
 int launch_gather(const GatherArgs &a, void *stream);
 int launch_icm(const IcmArgs &a, void *stream);

@@ -144,7 +144,9 @@ uint64_t shapes_sig(const pa_fused *f)
 {
     uint64_t h = 1469598103934665603ull;
     for (const auto &g : f->groups) {
-        const uint64_t v = (uint64_t)g.shape.W | (uint64_t)g.shape.threads << 8 | (uint64_t)g.shape.direct << 24;
+        const uint64_t v = (uint64_t)g.shape.W | (uint64_t)g.shape.threads << 8 | (uint64_t)g.shape.direct << 24 |
+                           (uint64_t)g.shape.ahead << 25 | (uint64_t)g.shape.fuse << 26 |
+                           (uint64_t)g.shape.deg << 27;
         h = (h ^ v) * 1099511628211ull;
     }
     return h;
@@ -172,7 +174,7 @@ void shape_facts(const pa_fused *f, pa_fused::Group &g)
     g.blocks = (int)work_list(f, g).size();
     g.lds = 0;
     for (int i : g.members)
-        g.lds = std::max(g.lds, pa::sweep_bytes_lds(g.shape.W, 0, f->runs[i].s->n, f->runs[i].s->dmax));
+        g.lds = std::max(g.lds, g.shape.lds(f->runs[i].s->n, f->runs[i].s->dmax));
 }
 
 // Prepare every run of the groups in `which` (all if empty) for the group
@@ -214,7 +216,7 @@ pa_status prepare(pa_fused *f, unsigned char *ws, hipStream_t hs, const std::vec
             m.nblk = P.nblk;
             g.max_R = std::max(g.max_R, r.R);
             g.steps = std::max(g.steps, P.K);
-            g.lds = std::max(g.lds, pa::sweep_bytes_lds(g.shape.W, 0, r.s->n, r.s->dmax));
+            g.lds = std::max(g.lds, g.shape.lds(r.s->n, r.s->dmax));
         }
         const std::vector<int2> w = work_list(f, g);
         if (w.size() > g.work_cap) return fail(PA_EINVAL, "internal: work list exceeds its reservation");
@@ -248,8 +250,7 @@ pa_status enqueue_group_steps(pa_fused *f, pa_fused::Group &g, unsigned char *ws
     const pa::MultiRun *args = reinterpret_cast<const pa::MultiRun *>(ws + g.args_off);
     const int2 *work = reinterpret_cast<const int2 *>(ws + g.work_off);
     for (int k = k0; k < k1 && k < g.steps; ++k) {
-        LAUNCH_TRY(pa::launch_sweep_multi(g.shape.W, g.bsg, g.shape.direct != 0, g.shape.threads, g.blocks,
-                                          g.lds, args, work, k, hs));
+        LAUNCH_TRY(pa::launch_sweep_multi(g.shape.multi(g.blocks, g.lds), args, work, k, hs));
         LAUNCH_TRY(pa::launch_epilogue_multi((int)g.members.size(), g.max_R, args, k, hs));
     }
     return PA_OK;
@@ -327,7 +328,7 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
     // of 64, 128, 256, 512 that needs no more rounds (one barrier each) per
     // sweep than 512; a round covers one dependency level, and graphs of a
     // few thousand nodes have levels of 50 to 300 nodes.
-    std::vector<int> threads(count, 512);
+    std::vector<int> threads(count, 512), fuse(count, 0), tiled(count, 0), levels(count, 1);
     for (int i = 0; i < count; ++i) {
         pa_fused::Run &r = f->runs[i];
         Shape probe;
@@ -350,6 +351,19 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
         const long long r512 = rounds_at(512);
         for (int T : {256, 128, 64})
             if (rounds_at(T) <= r512) threads[i] = T;
+        levels[i] = p.n_levels;
+        tiled[i] = shared_tile_form(r.s, p.n_levels, f->max_lds, &fuse[i]);
+    }
+    int cus = 256, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+        (void)hipGetLastError();
+        cus = 256;
+    }
+    long long tiles4 = 0, tiles8 = 0;            // workgroups of a step, all groups
+    for (int i = 0; i < count; ++i) {
+        tiles4 += (f->runs[i].R + 3) / 4;
+        tiles8 += (f->runs[i].R + 7) / 8;
     }
     // Groups by record mode and graph size (the spin records of a tile take
     // n * W bytes of LDS, which with the threads sets how many workgroups
@@ -359,37 +373,58 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
         for (int sc = 3; sc >= 0; --sc) {
         pa_fused::Group g;
         g.bsg = bsg;
-        int T0 = 64;
+        int T0 = 64, deg = 0, all_fuse = 1;
+        double for_tile = 0, nodes = 0, lvls = 0;
         for (int i = 0; i < count; ++i)
             if ((f->runs[i].s->has_neg ? 2 : 0) == bsg && size_class(f->runs[i].s->n) == sc) {
                 g.members.push_back(i);
                 T0 = std::max(T0, threads[i]);
+                deg = std::max(deg, degree_class(f->runs[i].s->dmax));
+                all_fuse &= fuse[i];
+                for_tile += (tiled[i] ? 1 : -1) * f->runs[i].cost * f->runs[i].R;
+                nodes += f->runs[i].s->n;
+                lvls += levels[i];
             }
         if (g.members.empty()) continue;
         std::stable_sort(g.members.begin(), g.members.end(),
                          [&](int a, int b) { return f->runs[a].cost > f->runs[b].cost; });
+        // The form that suits most of the group's work; the tile form takes
+        // its threads from what is resident (tile_threads), the byte form
+        // from the levels.
+        const int ahead = for_tile > 0;
+        const long long per_level = (long long)(nodes / lvls);
+        int want = ahead && tiles4 <= cus ? 4 : 8;
         for (int W : kTileCand)
-            for (int T : {64, 128, 256, 512}) {
+            for (int T : {64, 128, 256, 512, 1024}) {
+                if (ahead ? T < 256 : T > 512) continue;
                 Shape sh;
                 sh.W = W;
                 sh.threads = T;
                 sh.bsg = bsg;
-                sh.direct = 1;
+                sh.ahead = ahead;
+                sh.direct = !ahead;
+                sh.deg = ahead ? deg : 0;
+                sh.fuse = ahead && W <= 8 && all_fuse;
                 bool ok = true;
+                int lds = 0;
                 for (int i : g.members) {
                     const pa_solver *s = f->runs[i].s;
-                    if (pa::sweep_bytes_lds(W, 0, s->n, s->dmax) > f->max_lds) ok = false;
-                    if (!direct_fits(s, W)) sh.direct = 0;
+                    lds = std::max(lds, sh.lds(s->n, s->dmax));
+                    if (!ahead && !direct_fits(s, W)) sh.direct = 0;
                 }
+                if (lds > f->max_lds) ok = false;
+                if (ok && ahead && W == want)
+                    T0 = tile_threads((int)(((W == 4 ? tiles4 : tiles8) + cus - 1) / cus), lds, f->max_lds, per_level);
                 if (ok) g.candidates.push_back(sh);
             }
         if (g.candidates.empty())
             return bail(fail(PA_ERANGE, "pa_fused_create: a graph does not fit LDS at any shared shape"));
-        // Untuned shape: 8 replicas per workgroup and the group's thread count
+        // Untuned shape: 8 replicas per workgroup (4 where all workgroups of
+        // the batch get a compute unit each then) and the group's thread count
         // when they fit, else the first fit.
         g.shape = g.candidates[0];
         for (const Shape &c : g.candidates)
-            if (c.W == 8 && c.threads == T0) g.shape = c;
+            if (c.W == want && c.threads == T0) g.shape = c;
         f->groups.push_back(std::move(g));
     }
 

@@ -77,11 +77,34 @@ struct Plan {
 };
 
 // A launch shape imposed on kernel 1 (multi-run launches share one shape):
-// replicas per workgroup, threads, record mode (0 unsigned, 2 sign bits) and
-// block-entry form (1 LDS byte offsets, 0 record indices).
+// replicas per workgroup, threads, record mode (0 unsigned, 2 sign bits); for
+// the byte form its block entries (1 LDS byte offsets, 0 record indices), for
+// the tile form (ahead) its counters and where it draws (Plan::deg, fuse).
 struct Shape {
-    int W = 8, threads = 512, bsg = 0, direct = 1;
+    int W = 8, threads = 512, bsg = 0, direct = 1, ahead = 0, deg = 0, fuse = 0;
+    int byte_W = 0, byte_threads = 0;   // ahead: the plan takes no less room than the byte form's with these
+    bool operator==(const Shape &o) const
+    {
+        return W == o.W && threads == o.threads && bsg == o.bsg && direct == o.direct && ahead == o.ahead &&
+               deg == o.deg && fuse == o.fuse;
+    }
+    int lds(int n, int dmax) const     // of a sweep workgroup
+    {
+        return ahead ? pa::sweep_tile_lds(W, 0, n, fuse) : pa::sweep_bytes_lds(W, 0, n, dmax);
+    }
+    pa::MultiShape multi(int blocks, int lds) const
+    {
+        return {W, bsg, ahead, direct, deg, fuse, threads, blocks, lds};
+    }
 };
+// The sweep order's dependency levels (Plan::n_levels, level_off, sched).
+void build_levels(const pa_solver *s, const int32_t *order, Plan &p);
+// Whether a run that shares launches is faster in the tile form, and whether
+// that form draws in registers then.
+bool shared_tile_form(const pa_solver *s, int n_levels, int max_lds, int *fuse);
+// Threads of a tile-form workgroup of `lds` bytes where `need` of them come to
+// a compute unit.
+int tile_threads(int need, int lds, int max_lds, long long per_level);
 
 // Counter class of the tile form for a maximum degree.
 inline int degree_class(int dmax) { return dmax <= 63 ? 0 : dmax <= 127 ? 1 : 2; }

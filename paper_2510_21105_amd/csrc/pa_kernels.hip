@@ -1200,6 +1200,20 @@ __global__ __launch_bounds__(1024) void sweep_bytes_kernel(SweepArgs a, const in
     sweep_bytes_tile<W, SG, DIRECT>(a, rounds, blocks, blk, nb, PRIO);
 }
 
+// The buffers of step k of a run that shares launches: they follow from the
+// parity of the step (the initial population is in X0/E0), and step 0 reads no
+// resampling parents.
+__device__ __forceinline__ void step_buffers(const MultiRun &m, int k, SweepArgs &a)
+{
+    const bool even = (k & 1) == 0;
+    a.k = k;
+    a.Xin = even ? m.X0 : m.X1;
+    a.X = even ? m.X1 : m.X0;
+    a.Ein = even ? m.E0 : m.E1;
+    a.E = even ? m.E1 : m.E0;
+    a.parent = k == 0 ? nullptr : m.epi.parent;
+}
+
 // One step of many runs in one launch: workgroup b takes the tile work[b] =
 // {run, tile} (run < 0: an empty slot), with the run's arguments from
 // runs[run]. Launch index t is step t - k_off of a run; its population
@@ -1216,13 +1230,7 @@ __global__ __launch_bounds__(1024) void sweep_bytes_multi_kernel(const MultiRun 
     const int k = t - m.k_off;
     if (k < 0 || k >= m.steps) return;
     SweepArgs a = m.sweep;
-    const bool even = (k & 1) == 0;
-    a.k = k;
-    a.Xin = even ? m.X0 : m.X1;
-    a.X = even ? m.X1 : m.X0;
-    a.Ein = even ? m.E0 : m.E1;
-    a.E = even ? m.E1 : m.E0;
-    a.parent = k == 0 ? nullptr : m.epi.parent;
+    step_buffers(m, k, a);
     sweep_bytes_tile<W, SG, DIRECT>(a, a.rounds, a.blocks, wk.y, m.nblk, false);
 }
 
@@ -1472,7 +1480,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
 #pragma unroll
     for (int b = 0; b < W; ++b) {
         const int r = r0 + b < a.R ? r0 + b : r0;
-        pr[b] = ident ? r : a.parent[r];
+        pr[b] = __builtin_amdgcn_readfirstlane(ident ? r : a.parent[r]);
         gA = (pr[b] >> 6) < gA ? (pr[b] >> 6) : gA;
         gB = (pr[b] >> 6) > gB ? (pr[b] >> 6) : gB;
     }
@@ -1571,7 +1579,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
                     const int i = base + u * nt + tid;
                     uint32_t v = 0;
                     if (i < n) {
-#pragma unroll
+#pragma unroll 1
                         for (int b = 0; b < W; ++b)
                             v |= (uint32_t)((a.Xin[(size_t)(pr[b] >> 6) * n + i] >> (pr[b] & 63)) & 1ull) << b;
                     }
@@ -2115,6 +2123,21 @@ __global__ __launch_bounds__(1024) void sweep_tile_kernel(SweepArgs a, const int
         return x * q + (x < rem ? x : rem) + (b >> 3);
     }();
     sweep_tile<W, SG, DEG, FUSE>(a, items, streams, blocks, blk, nb, PRIO);
+}
+
+// One step of many runs in one launch (sweep_bytes_multi_kernel's work list).
+template <int W, int SG, int DEG, bool FUSE>
+__global__ __launch_bounds__(1024) void sweep_tile_multi_kernel(const MultiRun *__restrict__ runs,
+                                                                const int2 *__restrict__ work, int t)
+{
+    const int2 wk = work[blockIdx.x];
+    if (wk.x < 0) return;
+    const MultiRun &m = runs[wk.x];
+    const int k = t - m.k_off;
+    if (k < 0 || k >= m.steps) return;
+    SweepArgs a = m.sweep;
+    step_buffers(m, k, a);
+    sweep_tile<W, SG, DEG, FUSE>(a, a.items, a.streams, a.blocks, wk.y, m.nblk, false);
 }
 
 // ---------------------------------------------------------------------------
@@ -3098,41 +3121,59 @@ int launch_sweep_tile(int W, int sg, int deg, int fuse, int threads, int nblk, i
 }
 
 template <int W, int SG, bool D>
-static int launch_multi_t(int threads, int blocks, int lds, const MultiRun *runs, const int2 *work, int k,
-                          void *stream)
+static int launch_multi_t(const MultiShape &sh, const MultiRun *runs, const int2 *work, int k, void *stream)
 {
     static int configured[kMaxDevices] = {};
-    if (allow_lds(reinterpret_cast<const void *>(&sweep_bytes_multi_kernel<W, SG, D>), configured, lds,
+    if (allow_lds(reinterpret_cast<const void *>(&sweep_bytes_multi_kernel<W, SG, D>), configured, sh.lds,
                   "hipFuncSetAttribute(sweep_bytes_multi)"))
         return -1;
-    hipLaunchKernelGGL((sweep_bytes_multi_kernel<W, SG, D>), dim3(blocks), dim3(threads), lds,
+    hipLaunchKernelGGL((sweep_bytes_multi_kernel<W, SG, D>), dim3(sh.blocks), dim3(sh.threads), sh.lds,
                        (hipStream_t)stream, runs, work, k);
     return check("sweep_bytes_multi_kernel");
 }
 
-template <int W>
-static int launch_multi_w(int sgn, bool direct, int threads, int blocks, int lds, const MultiRun *runs,
-                          const int2 *work, int k, void *stream)
+template <int W, int SG, int DEG, bool FUSE>
+static int launch_multi_tile_t(const MultiShape &sh, const MultiRun *runs, const int2 *work, int k, void *stream)
 {
-    if (sgn == 2) return direct ? launch_multi_t<W, 2, true>(threads, blocks, lds, runs, work, k, stream)
-                                : launch_multi_t<W, 2, false>(threads, blocks, lds, runs, work, k, stream);
-    return direct ? launch_multi_t<W, 0, true>(threads, blocks, lds, runs, work, k, stream)
-                  : launch_multi_t<W, 0, false>(threads, blocks, lds, runs, work, k, stream);
+    static int configured[kMaxDevices] = {};
+    if (allow_lds(reinterpret_cast<const void *>(&sweep_tile_multi_kernel<W, SG, DEG, FUSE>), configured, sh.lds,
+                  "hipFuncSetAttribute(sweep_tile_multi)"))
+        return -1;
+    hipLaunchKernelGGL((sweep_tile_multi_kernel<W, SG, DEG, FUSE>), dim3(sh.blocks), dim3(sh.threads), sh.lds,
+                       (hipStream_t)stream, runs, work, k);
+    return check("sweep_tile_multi_kernel");
 }
 
-int launch_sweep_multi(int W, int sgn, bool direct, int threads, int blocks, int lds, const MultiRun *runs,
-                       const int2 *work, int k, void *stream)
+template <int W, int SG>
+static int launch_multi_w(const MultiShape &sh, const MultiRun *runs, const int2 *work, int k, void *stream)
 {
-    if (sgn == 1) {
-        snprintf(g_err, sizeof g_err, "multi-run sweeps take unsigned records or sign bits");
+    if (!sh.ahead)
+        return sh.direct ? launch_multi_t<W, SG, true>(sh, runs, work, k, stream)
+                         : launch_multi_t<W, SG, false>(sh, runs, work, k, stream);
+    if (sh.fuse) {
+        if constexpr (W <= 8) return launch_multi_tile_t<W, SG, 0, true>(sh, runs, work, k, stream);
+        snprintf(g_err, sizeof g_err, "draws in registers take 4 or 8 replicas");
         return -1;
     }
-    switch (W) {
-    case 4: return launch_multi_w<4>(sgn, direct, threads, blocks, lds, runs, work, k, stream);
-    case 8: return launch_multi_w<8>(sgn, direct, threads, blocks, lds, runs, work, k, stream);
-    case 16: return launch_multi_w<16>(sgn, direct, threads, blocks, lds, runs, work, k, stream);
+    return sh.deg == 0 ? launch_multi_tile_t<W, SG, 0, false>(sh, runs, work, k, stream)
+                       : launch_multi_tile_t<W, SG, 1, false>(sh, runs, work, k, stream);
+}
+
+int launch_sweep_multi(const MultiShape &sh, const MultiRun *runs, const int2 *work, int k, void *stream)
+{
+    if ((sh.sgn != 0 && sh.sgn != 2) || (sh.ahead && sh.deg > 1)) {
+        snprintf(g_err, sizeof g_err, "multi-run sweeps take unsigned records or sign bits, degrees up to 127");
+        return -1;
+    }
+    switch (sh.W) {
+    case 4: return sh.sgn ? launch_multi_w<4, 2>(sh, runs, work, k, stream)
+                          : launch_multi_w<4, 0>(sh, runs, work, k, stream);
+    case 8: return sh.sgn ? launch_multi_w<8, 2>(sh, runs, work, k, stream)
+                          : launch_multi_w<8, 0>(sh, runs, work, k, stream);
+    case 16: return sh.sgn ? launch_multi_w<16, 2>(sh, runs, work, k, stream)
+                           : launch_multi_w<16, 0>(sh, runs, work, k, stream);
     default:
-        snprintf(g_err, sizeof g_err, "unsupported byte-tile width %d", W);
+        snprintf(g_err, sizeof g_err, "unsupported tile width %d", sh.W);
         return -1;
     }
 }

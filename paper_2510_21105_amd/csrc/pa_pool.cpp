@@ -45,11 +45,9 @@ size_t slot_bytes()
 size_t lane_bytes() { return kSlots * slot_bytes(); }
 
 struct Key {
-    int bsg = 0, W = 8, direct = 1, threads = 256, cls = 1;
-    bool operator==(const Key &o) const
-    {
-        return bsg == o.bsg && W == o.W && direct == o.direct && threads == o.threads && cls == o.cls;
-    }
+    Shape shape;
+    int cls = 1;                       // workgroups that a compute unit's LDS holds
+    bool operator==(const Key &o) const { return shape == o.shape && cls == o.cls; }
 };
 
 }  // namespace
@@ -223,39 +221,54 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     j.inst = run->instance;
     j.K = run->schedule->n_steps;
     // Shape: 8 replicas per workgroup where a tile's records fit LDS, else 4;
-    // sign-bit entries for graphs with -1 weights; LDS offsets as entries
-    // where they fit 16 bits; threads: the smallest of 64, 128, 256, 512 whose
-    // rounds per sweep (one per dependency-level chunk) are no more than
-    // with 512.
+    // sign-bit entries for graphs with -1 weights. The form of
+    // shared_tile_form, with the threads of a busy compute unit (as many
+    // workgroups as its LDS holds); in the byte form LDS offsets as entries
+    // where they fit 16 bits, and the smallest of 64, 128, 256, 512 threads
+    // whose rounds per sweep (one per dependency-level chunk) are no more
+    // than with 512.
     const pa_solver *s = run->solver;
-    j.shape.bsg = s->has_neg ? 2 : 0;
-    j.shape.W = pa::sweep_bytes_lds(8, 0, s->n, s->dmax) <= p->max_lds ? 8 : 4;
-    j.shape.threads = 512;
-    j.shape.direct = pa::kBytesRecBase + (size_t)(s->n + 1) * j.shape.W <= 0xFFFF;
+    Shape byte;
+    byte.bsg = s->has_neg ? 2 : 0;
+    byte.W = byte.lds(s->n, s->dmax) <= p->max_lds ? 8 : 4;
+    byte.threads = 512;
+    byte.direct = pa::kBytesRecBase + (size_t)(s->n + 1) * byte.W <= 0xFFFF;
     Plan plan;
-    st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape);
-    if (st != PA_OK) return st;
-    {
-        auto rounds_at = [&](int T) {
-            long long n = 0;
-            for (int l = 0; l < plan.n_levels; ++l) n += (plan.level_off[l + 1] - plan.level_off[l] + T - 1) / T;
-            return n;
-        };
-        const long long r512 = rounds_at(512);
-        for (int T : {256, 128, 64})
-            if (rounds_at(T) <= r512) j.shape.threads = T;
-        if (j.shape.threads != 512) {
-            plan = Plan();
-            st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape);
-            if (st != PA_OK) return st;
-        }
+    build_levels(s, j.sch.order, plan);
+    auto rounds_at = [&](int T) {
+        long long n = 0;
+        for (int l = 0; l < plan.n_levels; ++l) n += (plan.level_off[l + 1] - plan.level_off[l] + T - 1) / T;
+        return n;
+    };
+    const long long r512 = rounds_at(512);
+    for (int T : {256, 128, 64})
+        if (rounds_at(T) <= r512) byte.threads = T;
+    j.shape = byte;
+    Shape tile = byte;
+    tile.ahead = 1;
+    tile.W = 8;
+    tile.direct = 0;
+    tile.deg = degree_class(s->dmax);
+    tile.byte_W = byte.W;
+    tile.byte_threads = byte.threads;
+    if (s->dmax <= kMaxBytesDegree && shared_tile_form(s, plan.n_levels, p->max_lds, &tile.fuse)) {
+        const int fit = p->max_lds / tile.lds(s->n, s->dmax);
+        tile.threads = fit >= 4 ? 256 : fit >= 2 ? 512 : 1024;
+        if (fit >= 1) j.shape = tile;
     }
-    j.lds = pa::sweep_bytes_lds(j.shape.W, 0, s->n, s->dmax);
-    j.key.bsg = j.shape.bsg;
-    j.key.W = j.shape.W;
-    j.key.direct = j.shape.direct;
-    j.key.threads = j.shape.threads;
-    j.key.cls = std::min(8, p->max_lds / std::max(j.lds, 1));
+    plan = Plan();
+    st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape);
+    if (st == PA_OK && j.shape.ahead && align_up(plan.L.total) > p->bytes - p->heap_off) {
+        // No room for this form's plan: the byte form's may be smaller.
+        j.shape = byte;
+        plan = Plan();
+        st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape);
+    }
+    if (st != PA_OK) return st;
+    j.lds = j.shape.lds(s->n, s->dmax);
+    j.key.shape = j.shape;
+    j.key.shape.byte_W = j.key.shape.byte_threads = 0;
+    j.key.cls = std::min(j.shape.ahead ? 4 : 8, p->max_lds / std::max(j.lds, 1));
     j.need = align_up(plan.L.total);
     if (j.need > p->bytes - p->heap_off)
         return fail(PA_EWORKSPACE, "run needs %zu bytes, more than the pool's %zu", j.need,
@@ -372,7 +385,7 @@ pa_status rebuild(pa_pool *p, int li)
         lds = std::max(lds, j.lds);
         max_R = std::max(max_R, j.R);
     }
-    const std::vector<int2> w = multi_work_list(nblk, L.key.W);
+    const std::vector<int2> w = multi_work_list(nblk, L.key.shape.W);
     const size_t ab = align_up(sizeof(pa::MultiRun) * mr.size());
     if (mr.size() > (size_t)kLaneMaxRuns || w.size() > (size_t)kLaneMaxWork)
         return fail(PA_ERANGE, "internal: lane tables overflow");
@@ -395,8 +408,7 @@ pa_status iterate(pa_pool *p, int li)
     pa_pool::Lane &L = p->lanes[li];
     const pa::MultiRun *args = reinterpret_cast<const pa::MultiRun *>(p->ws + L.args);
     const int2 *work = reinterpret_cast<const int2 *>(p->ws + L.work);
-    LAUNCH_TRY(pa::launch_sweep_multi(L.key.W, L.key.bsg, L.key.direct != 0, L.key.threads, L.blocks, L.lds, args,
-                                      work, L.iter, L.st));
+    LAUNCH_TRY(pa::launch_sweep_multi(L.key.shape.multi(L.blocks, L.lds), args, work, L.iter, L.st));
     LAUNCH_TRY(pa::launch_epilogue_multi((int)L.runs.size(), L.max_R, args, L.iter, L.st));
     HIP_TRY(hipEventRecord(L.slot_ev[L.slot], L.st));
     L.slot_pending[L.slot] = true;
