@@ -390,9 +390,10 @@ static void build_blocks(const pa_solver *s, Plan &p, int direct)
         }
 }
 
-bool pa_host::fuse_draws(int n, int n_levels, int dmax)
+bool pa_host::fuse_draws(const pa_solver *s, int n_levels)
 {
-    return dmax <= 8 && n >= 256 * n_levels;
+    return (s->dmax == 4 || s->dmax == 2) && s->nnz == (long long)s->n * s->dmax && s->n + 256 <= 0x7FFF &&
+           s->n >= 256 * n_levels;
 }
 
 // The tile form's item streams and blocks (their layout is described at
@@ -414,7 +415,7 @@ static void build_tile_plan(const pa_solver *s, Plan &p)
     // lanes. An item that leaves half its lanes free spreads its nodes over
     // more of them down to one row a lane: the chain of a level shortens with
     // the entries read in turn.
-    const bool long_head = p.fuse || p.bsg != 0;
+    const bool long_head = p.bsg != 0;
     const int e0 = long_head ? 4 : 6;
     const int most = p.fuse ? e0 : p.bsg == 2 ? 16 : e0 + 16, lp_max = d16 ? 6 : 4;
     struct Item {
@@ -501,6 +502,26 @@ static void build_tile_plan(const pa_solver *s, Plan &p)
         for (int r = 0; r < it.rows; ++r)
             for (int q = 0; q < rec_words; ++q) at(r, lanes)[q] = (uint16_t)dummy;
         uint16_t *spare = at(0, lanes);
+        // A FUSE block: {record, node}, a byte per neighbour where its edge is
+        // negative, four neighbours. A dummy's first degree / 2 are.
+        const uint16_t neg_byte = W == 4 ? 0x01 : 0x11;
+        if (p.fuse) {
+            spare[1] = 0;
+            spare[2] = (uint16_t)(s->dmax == 4 ? neg_byte * 0x0101 : neg_byte);
+            spare[3] = 0;
+            for (int lane = 0; lane < lanes; ++lane) {
+                const int i = p.sched[it.slot + lane], first = s->row_ptr[i];
+                uint16_t *h = at(0, lane);
+                for (int q = 0; q < rec_words; ++q) h[q] = (uint16_t)pa::tile_record(W, p.fuse, i);
+                h[1] = (uint16_t)i;
+                h[2] = h[3] = 0;
+                for (int q = 0; q < s->dmax; ++q) {
+                    h[4 + q] = (uint16_t)pa::tile_record(W, p.fuse, s->col[first + q]);
+                    if (q >= s->npos[i]) h[2 + q / 2] = (uint16_t)(h[2 + q / 2] | neg_byte << 8 * (q % 2));
+                }
+            }
+            continue;
+        }
         spare[1] = 0;
         if (long_head) {
             spare[2] = 0;
@@ -703,16 +724,23 @@ static size_t tile_bytes(const pa_solver *s, const Plan &p)
            align_up(sizeof(int) * p.streams.size()) + tail_bytes(s, p, sizeof(uint32_t));
 }
 
-// A compute unit holds 16 waves of the tile kernel; a workgroup takes its share
-// of them (n = 4,000, degree 12, R = 16,384, four resident: 873 with 256
-// threads, 1,145 with 512; R = 1,024, one resident, 100 x 100 torus: 125 with
-// 1,024, 140 with 512). Small levels have no use for more than 512 threads (n =
-// 800: 123 with either), levels of thousands of nodes none for less (the torus
-// at R = 8,192: 625 with 512, 677 with 256).
-int pa_host::tile_threads(int need, int lds, int max_lds, long long per_level)
+// A compute unit holds 16 to 24 waves of the tile kernel; a workgroup takes its
+// share of them (n = 4,000, degree 12, R = 16,384, four resident: 873 with 256
+// threads, 1,145 with 512). One alone takes 1,024, but small levels have no use
+// for more than 512 (n = 800: 123 with either; n = 4,000, degree 8: 164 and 171).
+// With draws in registers it holds 32 waves, best shared by up to three or
+// four workgroups of 512 (100 x 100 torus, R = 16,384: 455, with 256 threads
+// 471, with 1,024 568; R = 2,048, one resident: 91 with 512, 82 with 1,024), or
+// by two of 768 (140 x 140 torus, R = 8,192: 472, with 512 489, with 1,024
+// 542). Two that are all there is keep the 1,024 threads that a workgroup of
+// that size has always had (R = 4,096: 283, with 768 251).
+int pa_host::tile_threads(int need, int lds, int max_lds, long long per_level, int fuse)
 {
-    const int res = std::min(need, max_lds / lds);
-    return res <= 1 ? (per_level >= 100 ? 1024 : 512) : res == 2 || per_level >= 1000 ? 512 : 256;
+    const int fit = max_lds / lds, res = std::min(need, fit);
+    if (!fuse) return res <= 1 ? (per_level >= 100 ? 1024 : 512) : res == 2 ? 512 : 256;
+    if (per_level < 1000) return res <= 2 ? 512 : 256;
+    if (res <= 1 || (fit == 2 && need == 2)) return 1024;
+    return fit == 2 ? 768 : 512;
 }
 
 // As in take_tile_form, for launches that many runs share: the byte form keeps
@@ -721,7 +749,7 @@ int pa_host::tile_threads(int need, int lds, int max_lds, long long per_level)
 bool pa_host::shared_tile_form(const pa_solver *s, int n_levels, int max_lds, int *fuse)
 {
     if (s->has_neg && s->n + 256 > 0x7FFF) return false;
-    *fuse = fuse_draws(s->n, n_levels, s->dmax);
+    *fuse = fuse_draws(s, n_levels);
     return *fuse || s->dmax > kBytesRegDegree || s->n / n_levels <= 350 ||
            (2 * pa::sweep_bytes_lds(8, 0, s->n, s->dmax) > max_lds && 2 * pa::sweep_tile_lds(8, 0, s->n, 0) <= max_lds);
 }
@@ -747,7 +775,8 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
     p.bsg = !p.sgn ? 0
             : s->dmax <= 8 || p.deg != 0 || 2 * pa::sweep_tile_lds(8, 1, n, 0) > max_lds ? 2 : 1;
     const int comp = p.bsg == 1 ? 1 : 0;
-    p.fuse = p.bsg != 1 && tile != 16 && fuse_draws(n, p.n_levels, s->dmax);
+    p.fuse = tile != 16 && fuse_draws(s, p.n_levels);
+    if (p.fuse) p.bsg = 2;          // (unsigned too: no sign bit is set then)
     auto lds = [&](int W) { return pa::sweep_tile_lds(W, comp, n, p.fuse); };
     // Shape. A sweep is a chain of levels, so it takes as long for one
     // workgroup as for all that are resident: the narrowest tile whose
@@ -764,7 +793,7 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
     }
     if (lds(p.W) > max_lds) return false;
     p.nblk = (p.R + p.W - 1) / p.W;
-    if (sch->wg_threads == 0) p.threads = tile_threads((p.nblk + cus - 1) / cus, lds(p.W), max_lds, per_level);
+    if (sch->wg_threads == 0) p.threads = tile_threads((p.nblk + cus - 1) / cus, lds(p.W), max_lds, per_level, p.fuse);
     // Form. The tile form shortens the chain of a level, and long rows spread
     // over lanes (n = 800, R = 1,024: 187 -> 131 at degree 12, 2,870 -> 380
     // at 48, where rows run past the general form's registers; degree 200 on
@@ -886,7 +915,8 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
         if (!force->ahead && force->direct && pa::kBytesRecBase + (size_t)(n + 1) * force->W > 0xFFFF)
             return fail(PA_ERANGE, "graph of %d nodes too large for offset entries at tile %d", n, force->W);
         if (force->ahead && (force->deg < degree_class(s->dmax) ||
-                             (force->fuse && (force->deg != 0 || s->dmax > 8 || force->W > 8))))
+                             (force->fuse && (force->deg != 0 || force->bsg != 2 || force->W > 8 ||
+                                              !fuse_draws(s, 1)))))
             return fail(PA_EINVAL, "shared launch counters %d do not suit this graph", force->deg);
         p.kind = 1;
         p.W = force->W;

@@ -395,7 +395,7 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
         const long long per_level = (long long)(nodes / lvls);
         int want = ahead && tiles4 <= cus ? 4 : 8;
         for (int W : kTileCand)
-            for (int T : {64, 128, 256, 512, 1024}) {
+            for (int T : {64, 128, 256, 512, 768, 1024}) {
                 if (ahead ? T < 256 : T > 512) continue;
                 Shape sh;
                 sh.W = W;
@@ -404,7 +404,7 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
                 sh.ahead = ahead;
                 sh.direct = !ahead;
                 sh.deg = ahead ? deg : 0;
-                sh.fuse = ahead && W <= 8 && all_fuse;
+                sh.fuse = ahead && W <= 8 && bsg == 2 && all_fuse;
                 bool ok = true;
                 int lds = 0;
                 for (int i : g.members) {
@@ -414,7 +414,8 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
                 }
                 if (lds > f->max_lds) ok = false;
                 if (ok && ahead && W == want)
-                    T0 = tile_threads((int)(((W == 4 ? tiles4 : tiles8) + cus - 1) / cus), lds, f->max_lds, per_level);
+                    T0 = tile_threads((int)(((W == 4 ? tiles4 : tiles8) + cus - 1) / cus), lds, f->max_lds, per_level,
+                                      sh.fuse);
                 if (ok) g.candidates.push_back(sh);
             }
         if (g.candidates.empty())

@@ -104,12 +104,12 @@ void build_levels(const pa_solver *s, const int32_t *order, Plan &p);
 bool shared_tile_form(const pa_solver *s, int n_levels, int max_lds, int *fuse);
 // Threads of a tile-form workgroup of `lds` bytes where `need` of them come to
 // a compute unit.
-int tile_threads(int need, int lds, int max_lds, long long per_level);
+int tile_threads(int need, int lds, int max_lds, long long per_level, int fuse);
 
 // Counter class of the tile form for a maximum degree.
 inline int degree_class(int dmax) { return dmax <= 63 ? 0 : dmax <= 127 ? 1 : 2; }
-// Whether a sweep of n nodes in n_levels dependency levels draws in registers.
-bool fuse_draws(int n, int n_levels, int dmax);
+// Whether the tile form draws in registers for this graph and order.
+bool fuse_draws(const pa_solver *s, int n_levels);
 
 pa_status check_schedule(const pa_solver *s, const pa_schedule *sch, int R);
 // room: workspace bytes at hand (a form that needs more than another is passed

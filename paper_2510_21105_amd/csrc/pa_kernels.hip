@@ -1259,25 +1259,31 @@ __global__ __launch_bounds__(1024) void sweep_bytes_multi_kernel(const MultiRun 
 //            XOR-and-add of the records; m = 2 v - d is compared with q for
 //            4 replicas in one subtraction. No table, no draw on the chain.
 //
-// Graphs of degree at most 8 with a few large levels (tori) have waves enough
-// and take the FUSE form, which draws in registers in the level's own pass
-// (100 x 100 torus, R = 16,384: 627 us a step of 5 sweeps with the byte
-// form, 583 with this one).
+// Regular graphs of degree 4 or 2 with a few large levels (tori) have waves
+// enough, and their time is the instructions they issue and the LDS reads:
+// they take the FUSE form, which draws in registers in the level's own pass.
+// m is 2 or 4 uphill, so a draw counts the two thresholds above it, and 8
+// replicas are tested as the nibbles of one word (100 x 100 torus, R = 16,384:
+// 627 us a step of 5 sweeps with the byte form, 583
+// with tabled draws in registers, 490 with this one).
 //
 // Each wave walks a stream of items (item_word), dealt out by the host: nodes
 // of a level to decide, or 64 slots of the next chunk to draw, and where a
 // barrier or a change of buffer half follows. An item's block holds, row by
-// row, one uint4 per lane (coalesced): u16 {record, degree} and, where it is
-// read (FUSE, signed graphs), {node, sign bits or complement record}, then the
-// neighbours' record numbers, padded with the node's own record (x ^ x adds
-// nothing); a draw item's block is the nodes' numbers. Lanes past the item's
-// last node read the block's spare lane, a dummy node of degree 0. Every wave
+// row, one uint4 per lane (coalesced): u16 {record, degree} and, for signed
+// graphs, {node, sign bits or complement record}, then the neighbours' record
+// numbers, padded with the node's own record (x ^ x adds nothing); a draw
+// item's block is the nodes' numbers. The FUSE form's has {record, node}, a
+// byte per neighbour that is ONE's where the weight is negative, and four
+// neighbours. Lanes past the item's last node read the block's spare lane, a
+// dummy node of degree 0 (FUSE: with half its edges broken). Every wave
 // has a dummy record of its own: a dummy lane reads its record twice, as its
 // own and as its neighbours', and no other wave may write in between.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kTabLo = 0x3F80;     // bucket entry of draw 1.0f: float bits >> 16, low 3 bits clear
 constexpr uint32_t kTabHi = 0x4F88;     // past the entry of 2^32
 constexpr uint32_t kTileLow = 1024;     // below: entry of draw 0, energies, counters, thresholds
+constexpr uint32_t kFuseLow = 256;      // records of the FUSE form: four workgroups of 10,000 nodes a CU
 constexpr uint32_t kEdAt = 16, kCntAt = 144, kMultiAt = 160, kThrAt = 512;
 static_assert(kThrAt + 4 * 127 <= kTileLow, "threshold row");
 
@@ -1291,14 +1297,10 @@ struct TileRec {
 };
 
 // LDS address of record x. The draw buffer fills [kTileLow, kTabLo) and the
-// records follow the bucket table; without a buffer (FUSE) the records start
-// at kTileLow and step over the table.
+// records follow the bucket table; the FUSE form has neither.
 __host__ __device__ inline uint32_t tile_addr(int W, int fuse, uint32_t x)
 {
-    const uint32_t stride = W == 16 ? 8u : 4u;
-    if (!fuse) return kTabHi + x * stride;
-    const uint32_t at = kTileLow + x * stride;
-    return at < kTabLo ? at : at + (kTabHi - kTabLo);
+    return (fuse ? kFuseLow : kTabHi) + x * (W == 16 ? 8u : 4u);
 }
 
 int tile_record(int W, int fuse, int x) { return (int)(tile_addr(W, fuse, (uint32_t)x) >> (W == 16 ? 3 : 2)); }
@@ -1311,8 +1313,7 @@ int item_word(int last, int slot, int rows, int lp, int kind)
 
 int sweep_tile_lds(int W, int comp, int n, int fuse)
 {
-    const uint32_t end = tile_addr(W, fuse, (uint32_t)((comp ? 2 * n : n) + kMaxThreads / 64));
-    return (int)((end > kTabHi ? end : kTabHi) + 15u & ~15u);
+    return (int)(tile_addr(W, fuse, (uint32_t)((comp ? 2 * n : n) + kMaxThreads / 64)) + 15u & ~15u);
 }
 
 // Slots (multiple of 64) the draw buffer holds: 4 bytes per slot and 4
@@ -1399,6 +1400,37 @@ __host__ __device__ inline uint32_t bucket_last(int b)
     return (uint32_t)(B - 1 - half);
 }
 
+// Bytes: the number of the two thresholds above each of four draws. (One
+// block: a compare's mask is read two instructions later at the earliest.)
+__device__ __forceinline__ uint32_t below_two(const U4 &x, uint32_t ta, uint32_t tb)
+{
+    uint32_t q0, q1, q2, q3;
+    uint64_t a0, a1, a2, a3, b0, b1, b2, b3;
+    asm("v_cmp_gt_u32_e64 %4, %12, %14\n\t"
+        "v_cmp_gt_u32_e64 %5, %12, %15\n\t"
+        "v_cmp_gt_u32_e64 %6, %12, %16\n\t"
+        "v_cmp_gt_u32_e64 %7, %12, %17\n\t"
+        "v_cmp_gt_u32_e64 %8, %13, %14\n\t"
+        "v_cmp_gt_u32_e64 %9, %13, %15\n\t"
+        "v_cmp_gt_u32_e64 %10, %13, %16\n\t"
+        "v_cmp_gt_u32_e64 %11, %13, %17\n\t"
+        "v_cndmask_b32_e64 %0, 0, 1, %4\n\t"
+        "v_cndmask_b32_e64 %1, 0, 1, %5\n\t"
+        "v_cndmask_b32_e64 %2, 0, 1, %6\n\t"
+        "v_cndmask_b32_e64 %3, 0, 1, %7\n\t"
+        "v_addc_co_u32_e64 %0, %4, 0, %0, %8\n\t"
+        "v_addc_co_u32_e64 %1, %5, 0, %1, %9\n\t"
+        "v_addc_co_u32_e64 %2, %6, 0, %2, %10\n\t"
+        "v_addc_co_u32_e64 %3, %7, 0, %3, %11\n\t"
+        "v_lshl_or_b32 %0, %1, 8, %0\n\t"
+        "v_lshl_or_b32 %2, %3, 8, %2\n\t"
+        "v_lshl_or_b32 %0, %2, 16, %0"
+        : "=&v"(q0), "=&v"(q1), "=&v"(q2), "=&v"(q3), "=&s"(a0), "=&s"(a1), "=&s"(a2), "=&s"(a3), "=&s"(b0),
+          "=&s"(b1), "=&s"(b2), "=&s"(b3)
+        : "s"(ta), "s"(tb), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w));
+    return q0;
+}
+
 // The table entry that holds draw d.
 __device__ __forceinline__ uint32_t draw_entry(uint32_t d)
 {
@@ -1434,12 +1466,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     constexpr int NR = TR::words;               // record words
     constexpr int NQ = W / 4;                   // Philox calls per node
     constexpr int ND = D16 ? W / 2 : W / 4;     // decision words
-    constexpr bool LONG = FUSE || SG != 0;      // block header of 4 u16, else 2
+    constexpr bool LONG = SG != 0;              // block header of 4 u16, else 2
     constexpr int E0 = LONG ? 4 : 6;            // entries of a block's first row
     constexpr uint32_t ONE = TR::one;
     constexpr uint32_t BIAS = D16 ? 0x7FFFu : 0x7Fu;
     constexpr uint32_t BIASW = D16 ? 0x7FFF7FFFu : 0x7F7F7F7Fu;
     static_assert(!D16 || W == 4, "16-bit counters take 4 replicas");
+    static_assert(!FUSE || (SG == 2 && DEG == 0 && W <= 8), "draws in registers: sign bits, one record word");
     const int gk = a.adapt ? a.as_state[3] : a.k;     // grid point of this step
     if (gk >= a.K) {
         // A finished run (adaptive steps past the last grid point): carry the
@@ -1488,7 +1521,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     const uint64_t *XA = a.Xin + (size_t)gA * n, *XB = a.Xin + (size_t)gB * n;
     const int level = a.as_state[0];
     const uint32_t *trow = a.thr32 + ((size_t)gk * a.lmax1 + level) * (size_t)(dmax + 1);
-    for (int m = tid; m < dmax; m += nt) Trow[m] = trow[m];
+    if constexpr (!FUSE)
+        for (int m = tid; m < dmax; m += nt) Trow[m] = trow[m];
     // Accept-all row (exp(-beta * 2m) rounds to 1 for every uphill move).
     const bool all = trow[dmax] != 0;
     // Energies: lane r of every wave carries replica r0 + r.
@@ -1504,7 +1538,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     if (lane < NR) lds_set(dummy + 4 * lane, 0u);
     __syncthreads();
     // Bucket table of the step's thresholds.
-    for (int b = tid - 1; b <= 512; b += nt) {
+    for (int b = FUSE ? 513 : tid - 1; b <= 512; b += nt) {
         const uint32_t at = b < 0 ? 0u : kTabLo + 8u * (uint32_t)b;
         uint32_t thr = 0, q = (uint32_t)dmax;
         if (!all) {
@@ -1526,7 +1560,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     // for every node: the half is picked by a uniform branch per slot, so a
     // spin costs one bit extract.
     {
-        constexpr int LB = 4;
+        constexpr int LB = W == 4 ? 4 : 2;      // (8 replicas: 4 in flight cost 20 registers)
         int psel[W];
 #pragma unroll
         for (int b = 0; b < W; ++b)
@@ -1686,12 +1720,77 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     unsigned int att_c = 0, acc_c = 0;
     int last0 = 0, last1 = 0;          // energy sums already taken from Ed
 
+    // The FUSE form: node degree 2 h, so m = 2 (v - h) and only T[2] and T[4]
+    // (h = 1: none) are compared. f is the number of them above the draw.
+    const uint32_t half = (uint32_t)dmax >> 1;
+    const uint32_t t2 = FUSE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)trow[1]) : 0u;
+    const uint32_t t4 = FUSE && half > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)trow[3]) : 0u;
+    const uint32_t topw = ONE * (W == 4 ? 0x7Fu : 7u), halfw = half * ONE;
+    const uint32_t upw = topw - halfw;              // v + upw: top bit of the field = uphill
+    const uint32_t allw = all ? halfw : 0u;         // every uphill move accepted
+    uint32_t zn = 0, zb[W / 4] = {};     // sums of v (h if rejected): fields, bytes
+    uint32_t real_top = 0;
+    for (int b = 0; b < W; ++b)
+        if (FUSE && r0 + b < a.R) real_top |= (W == 4 ? 0x80u : 8u) << TR::bit(b);
+    auto decide_even = [&](const TileBlk &c, uint32_t s) {
+        const uint32_t own = entry_addr<TR::shift, false>(c.r0.x);
+        const uint32_t X = lds_get(own);
+        const uint32_t y0 = lds_get(entry_addr<TR::shift, false>(c.r0.z));
+        const uint32_t y1 = lds_get(entry_addr<TR::shift, true>(c.r0.z));
+        const uint32_t y2 = lds_get(entry_addr<TR::shift, false>(c.r0.w));
+        const uint32_t y3 = lds_get(entry_addr<TR::shift, true>(c.r0.w));
+        // The reads above are in flight while the draws are computed.
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t Q = 0;
+#pragma unroll
+        for (int g = 0; g < NQ; ++g) {
+            const U4 o = philox10(U4{c.r0.x >> 16, s, k, rgrp0 + (uint32_t)g}, a.seed_lo, a.seed_hi);
+            const uint32_t q = below_two(o, t2, t4);
+            Q = g == 0 ? q : Q | q << 4;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        auto differ = [&](uint32_t y, uint32_t sel) {
+            const uint32_t sign = __builtin_amdgcn_perm(0u, c.r0.y, sel);
+            return (uint32_t)__builtin_amdgcn_bitop3_b32(y, X, sign, 0x96);
+        };
+        const uint32_t v = (differ(y0, 0u) + differ(y1, 0x01010101u)) +
+                           (differ(y2, 0x02020202u) + differ(y3, 0x03030303u));
+        const uint32_t w = v + upw;
+        const uint32_t r = w - Q - allw;            // top bit of the field: rejected
+        att_c += __builtin_popcount(w & real_top);
+        acc_c += __builtin_popcount(w & ~r & real_top);
+        const uint32_t f = (r >> (W == 4 ? 7 : 3)) & ONE;
+        lds_set(own, (uint32_t)__builtin_amdgcn_bitop3_b32(X, f, ONE, 0xD2));   // x ^ (~f & one)
+        const uint32_t full = (f << (W == 4 ? 8 : 4)) - f;
+        zn += bit_select(full, halfw, v);
+    };
+    // Two items' sums fit a nibble.
+    auto widen_even = [&]() {
+        if constexpr (W == 4) {
+            zb[0] += zn;
+        } else {
+            zb[0] += zn & 0x0F0F0F0Fu;
+            zb[W / 4 - 1] += (zn >> 4) & 0x0F0F0F0Fu;
+        }
+        zn = 0;
+    };
+
     // The wave's energy changes into the workgroup's sums of sweep parity p:
     // four lanes add their four words (64 items fill a 16-bit half then),
     // lane l goes on with word l mod 4, rows of 16 lanes add up by DPP.
     auto flush = [&](int p) {
         if (items_done == 0) return;
-        const int bias = (int)BIAS * 16 * items_done;
+        // (FUSE: sums of v, m = 2 (v - h).)
+        const int bias = (FUSE ? (int)half : (int)BIAS) * 16 * items_done;
+        if constexpr (FUSE) {
+            widen_even();
+#pragma unroll
+            for (int q = 0; q < W / 4; ++q) {
+                acc[2 * q] = zb[q] & 0x00FF00FFu;
+                acc[2 * q + 1] = (zb[q] >> 8) & 0x00FF00FFu;
+                zb[q] = 0;
+            }
+        }
         constexpr int L = NA < 4 ? NA : 4;              // lanes that share out the words
 #pragma unroll
         for (int base = 0; base < NA; base += 4) {
@@ -1713,8 +1812,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
                 x += (int)dpp<0x124>((uint32_t)x);                           // row_ror:4
                 return x + (int)dpp<0x128>((uint32_t)x);                     // row_ror:8
             };
-            e0 = 2 * (row(e0) - bias);
-            if constexpr (!D16) e1 = 2 * (row(e1) - bias);
+            e0 = (FUSE ? 4 : 2) * (row(e0) - bias);
+            if constexpr (!D16) e1 = (FUSE ? 4 : 2) * (row(e1) - bias);
             // Word t of a group of four words: replicas 4 (t / 2) + (t & 1)
             // and two after it (16-bit counters: replica t).
             const int r = 2 * base + (D16 ? l : 4 * (l >> 1) + (l & 1));
@@ -1730,13 +1829,11 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     auto decide = [&](const TileBlk &c, const uint32_t h, uint32_t s, uint32_t qbuf) {
         const uint32_t own = entry_addr<TR::shift, false>(c.r0.x);
         uint32_t d = c.r0.x >> 16;
-        const int rows = FUSE ? 1 : item_rows(h), lp = item_lp(h);
+        const int rows = item_rows(h), lp = item_lp(h);
         const Rec<NR> X = rec_load<NR>(own);
         uint32_t q[ND];
-        if constexpr (!FUSE) {
-            const uint32_t me = lp == 0 ? (uint32_t)lane : (uint32_t)lane >> lp;
-            q_at(qbuf + item_slot(h) * (4u * ND) + me * (4u * ND), q);
-        }
+        const uint32_t me = lp == 0 ? (uint32_t)lane : (uint32_t)lane >> lp;
+        q_at(qbuf + item_slot(h) * (4u * ND) + me * (4u * ND), q);
         auto lo = [&](uint32_t w) { return rec_load<NR>(entry_addr<TR::shift, false>(w)); };
         auto hi = [&](uint32_t w) { return rec_load<NR>(entry_addr<TR::shift, true>(w)); };
         // Sum of (neighbour ^ own) over a row's entries, the neighbour
@@ -1775,12 +1872,6 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
             y[5] = hi(c.r0.y);
         }
         y[0] = lo(c.r0.z); y[1] = hi(c.r0.z); y[2] = lo(c.r0.w); y[3] = hi(c.r0.w);
-        if constexpr (FUSE) {
-            // The reads above are in flight while the draws are computed.
-            __builtin_amdgcn_sched_barrier(0);
-            draws(c.r0.y & 0xFFFFu, s, q);
-            __builtin_amdgcn_sched_barrier(0);
-        }
         // The eight (half: four) records of a row.
         auto row = [&](const uint4 &r, Rec<NR> (&z)[8], bool half) {
             z[0] = lo(r.x); z[1] = hi(r.x); z[2] = lo(r.y); z[3] = hi(r.y);
@@ -1979,7 +2070,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
         const uint32_t x = (uint32_t)h0.y;
         const uint32_t kind = x & kItemKind;
         if (kind == (1u << 28)) {
-            decide(cur, x, s, qa);
+            if constexpr (FUSE) {
+                decide_even(cur, s);
+                ++items_done;
+            } else {
+                decide(cur, x, s, qa);
+            }
         } else if (!FUSE && kind != 0u) {
             // 2: of this sweep, 3: of the next (none after the last).
             const uint32_t s2 = s + (kind == kItemKind ? 1u : 0u);
@@ -2045,6 +2141,11 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
         for (int i = 0; i < sw.y; i += 2) {
             step(bA, bB, (uint32_t)s);
             step(bB, bA, (uint32_t)s);
+            if constexpr (FUSE) {
+                // 62 items of up to 4 fill a byte.
+                widen_even();
+                if (items_done >= 61) flush(s & 1);
+            }
         }
         hat -= 8u * (uint32_t)sw.y;                 // (the stream's end repeats its first items)
         flush(s & 1);
@@ -3088,7 +3189,6 @@ static int launch_tile_w(int sg, int deg, int fuse, int threads, int nblk, int l
     if (deg == 0 && fuse) {
         if constexpr (W <= 8) {
             if (sg == 2) return launch_tile_t<W, 2, 0, true>(threads, nblk, lds, a, stream);
-            if (sg == 0) return launch_tile_t<W, 0, 0, true>(threads, nblk, lds, a, stream);
         }
     } else if (deg == 0) {
         if (sg == 2) return launch_tile_t<W, 2, 0, false>(threads, nblk, lds, a, stream);
@@ -3151,8 +3251,8 @@ static int launch_multi_w(const MultiShape &sh, const MultiRun *runs, const int2
         return sh.direct ? launch_multi_t<W, SG, true>(sh, runs, work, k, stream)
                          : launch_multi_t<W, SG, false>(sh, runs, work, k, stream);
     if (sh.fuse) {
-        if constexpr (W <= 8) return launch_multi_tile_t<W, SG, 0, true>(sh, runs, work, k, stream);
-        snprintf(g_err, sizeof g_err, "draws in registers take 4 or 8 replicas");
+        if constexpr (W <= 8 && SG == 2) return launch_multi_tile_t<W, SG, 0, true>(sh, runs, work, k, stream);
+        snprintf(g_err, sizeof g_err, "draws in registers take 4 or 8 replicas and sign bits");
         return -1;
     }
     return sh.deg == 0 ? launch_multi_tile_t<W, SG, 0, false>(sh, runs, work, k, stream)

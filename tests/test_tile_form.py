@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2510_21105_amd import workloads as W
-from tests.test_gpu_parity import _compare, _cycle_with_hub, pa  # noqa: F401
+from tests.test_gpu_parity import _check_against_oracle, _compare, _cycle_with_hub, pa  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -46,15 +46,26 @@ def test_items_chunks_and_tiles(pa, tile, n, m, R, threads, signed):  # noqa: F8
     _compare(pa, g, wl, dict(tile_replicas=tile, wg_threads=threads), record=1)
 
 
-# Draws in registers: even and odd last items of a level, records on both
-# sides of the threshold table.
+# Draws in registers (regular, few levels): full and ragged last items of a
+# level, an odd count of them, more items than the sums hold between flushes.
 @pytest.mark.parametrize("L,R,signed,tile", [(32, 9, True, 0), (46, 17, False, 0), (62, 40, True, 4),
                                              (98, 12, False, 8), (34, 33, True, 8)])
 def test_large_levels_draw_in_registers(pa, L, R, signed, tile):  # noqa: F811
     g = W.torus(L, 7, signed)
     wl = dict(W.workload("torus100"), graph=g, R=R, betas=[0.0, 0.05, 0.7, 3.0], sweeps=3,
               order=W.checkerboard_order(L))
-    _compare(pa, g, wl, dict(tile_replicas=tile), record=1)
+    _compare(pa, g, wl, dict(tile_replicas=tile, wg_threads=64 if L == 98 else 0), record=1)
+
+
+# Degree 2: one threshold, two padding neighbours. Even nodes, then odd ones.
+@pytest.mark.parametrize("n,R,signed", [(514, 5, False), (1300, 40, True)])
+def test_rings_draw_in_registers(pa, n, R, signed):  # noqa: F811
+    i = np.arange(n)
+    w = 1 - 2 * ((i % 5 == 0) & signed).astype(np.int64)
+    g = W.from_edges(n, i, (i + 1) % n, w, f"ring{n}")
+    order = np.concatenate([i[::2], i[1::2]]).astype(np.int32)
+    wl = dict(W.workload("torus100"), graph=g, R=R, betas=[0.0, 0.3, 2.0], sweeps=3, order=order)
+    _compare(pa, g, wl, record=1)
 
 
 def test_workspace_without_room_for_the_tile_plan(pa):  # noqa: F811
@@ -72,3 +83,24 @@ def test_workspace_without_room_for_the_tile_plan(pa):  # noqa: F811
     for a, b in zip(s.population(), t.population()):
         assert np.array_equal(a, b)
     assert np.array_equal(s.step_stats(), t.step_stats()) and s.best_info() == t.best_info()
+
+
+def test_shared_launches(pa):  # noqa: F811
+    """Fused runs of one record mode and size class: degrees up to 100 (wide
+    counters for the whole group), small levels, a regular and a ragged
+    signed graph, before and after the shape is tuned."""
+    gs = [(_hub(300, 100, False), 33), (W.random_graph(700, 2800, 3, "f1"), 70), (_hub(500, 40, True), 9),
+          (W.torus(30, 5, True), 130), (W.torus(24, 6, True), 17)]
+    wls = [dict(W.workload("small800"), graph=g, R=R, betas=[0.0, 0.1, 0.8, 2.0][:k], sweeps=2, nl_period=0,
+                inst=q, order=W.checkerboard_order(int(g.n ** 0.5)) if "torus" in g.name else W.natural_order(g.n))
+           for q, ((g, R), k) in enumerate(zip(gs, (4, 3, 4, 2, 4)))]
+    params = [pa.params_from_workload(w, record=3) for w in wls]
+    solvers = [pa.Solver(w["graph"]) for w in wls]
+    fb = pa.FusedBatch(solvers, params)
+    fb.run()
+    for w, p, s in zip(wls, params, solvers):
+        _check_against_oracle(s, w, p)
+    fb.tune(probe_steps=1)
+    fb.run()
+    for w, p, s in zip(wls, params, solvers):
+        _check_against_oracle(s, w, p)
