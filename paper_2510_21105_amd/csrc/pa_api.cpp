@@ -409,15 +409,15 @@ static void build_tile_plan(const pa_solver *s, Plan &p)
         const int i = p.sched[slot];
         return s->row_ptr[i + 1] - s->row_ptr[i];
     };
-    // Entries a lane's block holds: 6 + 8 + 8 after a short header, 4 in the
-    // first row after a long one, 16 in all with sign bits, the first row
-    // alone with draws in registers. A node of a larger degree takes 2^lp
-    // lanes. An item that leaves half its lanes free spreads its nodes over
-    // more of them down to one row a lane: the chain of a level shortens with
-    // the entries read in turn.
+    // Entries a lane's block holds: 6 + 8 after a short header, 4 in the first
+    // row after a long one, 8 more with 16-bit counters (16 in all with sign
+    // bits), four with draws in registers. A node of a larger degree takes
+    // 2^lp lanes. An item that leaves half its lanes free spreads its nodes
+    // over more of them down to one row a lane: the chain of a level shortens
+    // with the entries read in turn.
     const bool long_head = p.bsg != 0;
     const int e0 = long_head ? 4 : 6;
-    const int most = p.fuse ? e0 : p.bsg == 2 ? 16 : e0 + 16, lp_max = d16 ? 6 : 4;
+    const int most = p.fuse ? e0 : !d16 ? e0 + 8 : p.bsg == 2 ? 16 : e0 + 16, lp_max = d16 ? 6 : 4;
     struct Item {
         int slot, count, lp, rows;
     };
@@ -724,34 +724,34 @@ static size_t tile_bytes(const pa_solver *s, const Plan &p)
            align_up(sizeof(int) * p.streams.size()) + tail_bytes(s, p, sizeof(uint32_t));
 }
 
-// A compute unit holds 16 to 24 waves of the tile kernel; a workgroup takes its
-// share of them (n = 4,000, degree 12, R = 16,384, four resident: 873 with 256
-// threads, 1,145 with 512). One alone takes 1,024, but small levels have no use
-// for more than 512 (n = 800: 123 with either; n = 4,000, degree 8: 164 and 171).
-// With draws in registers it holds 32 waves, best shared by up to three or
-// four workgroups of 512 (100 x 100 torus, R = 16,384: 455, with 256 threads
-// 471, with 1,024 568; R = 2,048, one resident: 91 with 512, 82 with 1,024), or
-// by two of 768 (140 x 140 torus, R = 8,192: 472, with 512 489, with 1,024
-// 542). Two that are all there is keep the 1,024 threads that a workgroup of
-// that size has always had (R = 4,096: 283, with 768 251).
+// A compute unit holds 24 to 32 waves of the tile kernel; a workgroup takes its
+// share of them. One alone takes 1,024 threads (n = 7,000, degree 4, R =
+// 1,024: 143, with 512 162), on small levels 512 (n = 4,000, degree 12, 125
+// nodes a level: 165, with 1,024 184). Two, and more on levels of more than
+// 160 nodes, take 512 each (n = 7,000, degree 12, R = 16,384: 1,298, with 256
+// 1,508; R = 4,096: 379, with 768 409), four on smaller levels 256 (n = 4,000,
+// degree 12, R = 16,384: 855, with 512 894).
+// With draws in registers up to three or four workgroups of 512 share a unit
+// (100 x 100 torus, R = 16,384: 455, with 256 threads 471, with 1,024 568; R =
+// 2,048, one resident: 91 with 512, 82 with 1,024), or two of 768 (140 x 140
+// torus, R = 8,192: 472, with 512 489, with 1,024 542). Two that are all there
+// is keep the 1,024 threads that a workgroup of that size has always had (R =
+// 4,096: 283, with 768 251).
 int pa_host::tile_threads(int need, int lds, int max_lds, long long per_level, int fuse)
 {
     const int fit = max_lds / lds, res = std::min(need, fit);
-    if (!fuse) return res <= 1 ? (per_level >= 100 ? 1024 : 512) : res == 2 ? 512 : 256;
+    if (!fuse) return res <= 1 ? (per_level > 160 ? 1024 : 512) : res == 2 || per_level > 160 ? 512 : 256;
     if (per_level < 1000) return res <= 2 ? 512 : 256;
     if (res <= 1 || (fit == 2 && need == 2)) return 1024;
     return fit == 2 ? 768 : 512;
 }
 
-// As in take_tile_form, for launches that many runs share: the byte form keeps
-// rows that its registers hold on levels of more than 350 nodes, unless its
-// records leave a compute unit one workgroup where the tile form's leave two.
-bool pa_host::shared_tile_form(const pa_solver *s, int n_levels, int max_lds, int *fuse)
+// Whether a run that shares launches can take the tile form (many generations
+// of workgroups, where it is the faster one: see take_tile_form).
+bool pa_host::shared_tile_form(const pa_solver *s, int n_levels, int *fuse)
 {
-    if (s->has_neg && s->n + 256 > 0x7FFF) return false;
     *fuse = fuse_draws(s, n_levels);
-    return *fuse || s->dmax > kBytesRegDegree || s->n / n_levels <= 350 ||
-           (2 * pa::sweep_bytes_lds(8, 0, s->n, s->dmax) > max_lds && 2 * pa::sweep_tile_lds(8, 0, s->n, 0) <= max_lds);
+    return !s->has_neg || s->n + 256 <= 0x7FFF;
 }
 
 // Whether a run takes the tile form, and its shape then; p comes with the
@@ -762,7 +762,6 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
     const int n = s->n, tile = sch->tile_replicas;
     const bool sign_ok = n + 256 <= 0x7FFF;
     if (p.sgn && !sign_ok) return false;
-    const int was_kind = p.kind, was_W = p.W;
     const bool was_turns = p.kind == 1 && p.W == 8 && p.nblk > cus && p.nblk <= 2 * cus;
     const long long per_level = n / p.n_levels;     // nodes a level, on average
     p.kind = 1;
@@ -793,22 +792,33 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
     }
     if (lds(p.W) > max_lds) return false;
     p.nblk = (p.R + p.W - 1) / p.W;
-    if (sch->wg_threads == 0) p.threads = tile_threads((p.nblk + cus - 1) / cus, lds(p.W), max_lds, per_level, p.fuse);
-    // Form. The tile form shortens the chain of a level, and long rows spread
-    // over lanes (n = 800, R = 1,024: 187 -> 131 at degree 12, 2,870 -> 380
-    // at 48, where rows run past the general form's registers; degree 200 on
-    // 1,000 nodes, the word kernel before: 47,440 -> 1,770), and its nibble
-    // records let 8 replicas stand where bytes leave room for 4 (n = 12,000,
-    // R = 4,096, degree 12: 843 -> 562). The general form keeps levels of
-    // many nodes, which fill its waves without drawing ahead: above about 350
-    // with 4 replicas (n = 20,000, degree 6, R = 1,024: 373 and 372; 467 a
-    // level: 158 and 165), above 256 with more (n = 7,000 in colouring order,
-    // 778 a level, R = 4,096: 264 and 306), and above 192 with its two
-    // workgroups a compute unit in issue-priority turns (n = 7,000, degree 12,
-    // 212 a level, R = 4,096: 408 and 412).
-    if (was_kind == 2 || p.fuse || s->dmax > kBytesRegDegree) return true;
-    if (was_W == 4 && p.W == 8 && p.nblk >= 2 * cus && 2 * lds(8) <= max_lds) return true;
-    return per_level <= (was_W == 4 ? 350 : was_turns ? 192 : 256);
+    if (sch->wg_threads == 0) {
+        p.threads = tile_threads((p.nblk + cus - 1) / cus, lds(p.W), max_lds, per_level, p.fuse);
+        // The 7,000-node runs keep the 448 threads that they are known by, and
+        // others of two workgroups a unit whose levels need no more rounds with
+        // them (n = 7,000, degree 12: 392, with 512 379; n = 4,000: 259, 261).
+        if (p.W == 8 && !p.fuse && p.threads == 512 && p.nblk > cus && p.nblk <= 2 * cus) {
+            auto rounds_at = [&](int T) {
+                long long r = 0;
+                for (int l = 0; l < p.n_levels; ++l) r += (p.level_off[l + 1] - p.level_off[l] + T - 1) / T;
+                return r;
+            };
+            if (rounds_at(448) <= rounds_at(512)) p.threads = 448;
+        }
+    }
+    // Form. The tile form shortens the chain of a level (n = 7,000, degree 12,
+    // R = 1,024: 272 -> 213; R = 4,096: 430 -> 392), spreads long rows over
+    // lanes (n = 800, R = 1,024, degree 48, where rows run past the byte
+    // form's registers: 2,870 -> 350; degree 200 on 1,000 nodes, the word
+    // kernel before: 47,440 -> 1,700), and its nibble records let 8 replicas
+    // stand where bytes leave room for 4 or for fewer workgroups (n = 12,000,
+    // R = 4,096, degree 4: 608 -> 481). The byte form keeps levels of many
+    // nodes where two of its 8-replica workgroups a compute unit are the whole
+    // launch: they fill its waves without drawing ahead (R = 4,096, n = 7,000
+    // in colouring order, degree 12, 778 a level: 300, tile form 330; n =
+    // 4,000, 444 a level: 217 with either; n = 7,000, degree 4, 467 a level: 320
+    // and 308; R = 16,384, 778 a level: 1,186 and 1,163).
+    return !(was_turns && per_level > 480 && !p.fuse && s->dmax <= kBytesRegDegree);
 }
 
 pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan &p, bool tables,

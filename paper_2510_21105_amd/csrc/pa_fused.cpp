@@ -352,7 +352,7 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
         for (int T : {256, 128, 64})
             if (rounds_at(T) <= r512) threads[i] = T;
         levels[i] = p.n_levels;
-        tiled[i] = shared_tile_form(r.s, p.n_levels, f->max_lds, &fuse[i]);
+        tiled[i] = shared_tile_form(r.s, p.n_levels, &fuse[i]);
     }
     int cus = 256, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||

@@ -1468,6 +1468,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     constexpr int ND = D16 ? W / 2 : W / 4;     // decision words
     constexpr bool LONG = SG != 0;              // block header of 4 u16, else 2
     constexpr int E0 = LONG ? 4 : 6;            // entries of a block's first row
+    constexpr int ROWS = FUSE ? 1 : D16 ? 3 : 2;    // rows of a block at most
     constexpr uint32_t ONE = TR::one;
     constexpr uint32_t BIAS = D16 ? 0x7FFFu : 0x7Fu;
     constexpr uint32_t BIASW = D16 ? 0x7FFF7FFFu : 0x7F7F7F7Fu;
@@ -1732,7 +1733,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     uint32_t real_top = 0;
     for (int b = 0; b < W; ++b)
         if (FUSE && r0 + b < a.R) real_top |= (W == 4 ? 0x80u : 8u) << TR::bit(b);
-    auto decide_even = [&](const TileBlk &c, uint32_t s) {
+    auto decide_even = [&](const TileBlk &c, uint32_t s, auto &&next) {
         const uint32_t own = entry_addr<TR::shift, false>(c.r0.x);
         const uint32_t X = lds_get(own);
         const uint32_t y0 = lds_get(entry_addr<TR::shift, false>(c.r0.z));
@@ -1741,6 +1742,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
         const uint32_t y3 = lds_get(entry_addr<TR::shift, true>(c.r0.w));
         // The reads above are in flight while the draws are computed.
         __builtin_amdgcn_sched_barrier(0);
+        next();
         uint32_t Q = 0;
 #pragma unroll
         for (int g = 0; g < NQ; ++g) {
@@ -1826,7 +1828,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     };
 
     // Decide one item: the nodes of a level that this wave takes together.
-    auto decide = [&](const TileBlk &c, const uint32_t h, uint32_t s, uint32_t qbuf) {
+    auto decide = [&](const TileBlk &c, const uint32_t h, uint32_t s, uint32_t qbuf, auto &&next) {
         const uint32_t own = entry_addr<TR::shift, false>(c.r0.x);
         uint32_t d = c.r0.x >> 16;
         const int rows = item_rows(h), lp = item_lp(h);
@@ -1836,6 +1838,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
         q_at(qbuf + item_slot(h) * (4u * ND) + me * (4u * ND), q);
         auto lo = [&](uint32_t w) { return rec_load<NR>(entry_addr<TR::shift, false>(w)); };
         auto hi = [&](uint32_t w) { return rec_load<NR>(entry_addr<TR::shift, true>(w)); };
+        // While the records are on their way: the next block's request.
+        auto meanwhile = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+            next();
+            __builtin_amdgcn_sched_barrier(0);
+        };
         // Sum of (neighbour ^ own) over a row's entries, the neighbour
         // complemented for a negative edge.
         auto add = [&](Rec<NR> &C, const Rec<NR> &y, int j) {
@@ -1901,23 +1909,23 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
         };
         // All records of the item are requested before the first is added.
         if (rows == 1) {
-            __builtin_amdgcn_sched_barrier(0);
+            meanwhile();
             add_y();
             both();
             widen(Ca, true);
-        } else if (rows == 2) {
+        } else if (ROWS == 2 || rows == 2) {
             Rec<NR> z[8];
             row(c.r1, z, false);
-            __builtin_amdgcn_sched_barrier(0);
+            meanwhile();
             add_y();
             add_row(z, E0, false);
             both();
             widen(Ca, true);
-        } else {
+        } else if constexpr (ROWS > 2) {
             Rec<NR> z[8], u[8];
             row(c.r1, z, false);
             row(c.r2, u, SG == 2);          // 16 sign bits: the row's second half is padding
-            __builtin_amdgcn_sched_barrier(0);
+            meanwhile();
             add_y();
             add_row(z, E0, false);
             both();
@@ -1959,26 +1967,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
         }
         const uint32_t Dm = D16 ? d | d << 16 : __builtin_amdgcn_perm(0u, d, 0u);
         const uint32_t c1 = BIASW - Dm;
-        uint32_t rj[ND];
+        uint32_t wt[ND], rj[ND];
 #pragma unroll
         for (int t = 0; t < ND; ++t) {
-            const uint32_t w = twice_plus(V[t], c1);    // bias + m, m = 2 v - d: top bit = uphill
+            const uint32_t w = wt[t] = twice_plus(V[t], c1);    // bias + m, m = 2 v - d: top bit = uphill
             // Top bit of r: m > q, the flip is rejected.
-            uint32_t r;
-            if constexpr (DEG == 1) r = ((w | 0x80808080u) - q[t]) & w;
-            else r = w - q[t];
-            rj[t] = r;
-            att_c += __builtin_popcount(w & real[t]);
-            acc_c += __builtin_popcount(w & ~r & real[t]);
-            if constexpr (D16) {
-                const uint32_t z = bit_select(__builtin_amdgcn_perm(0u, r, 0x09090808u), BIASW, w);
-                acc[t] += z & 0xFFFFu;
-                acc[t + 2] += z >> 16;
-            } else {
-                const uint32_t z = bit_select(__builtin_amdgcn_perm(r << 8, r, 0x090B080Au), BIASW, w);
-                acc[2 * t] += z & 0x00FF00FFu;
-                acc[2 * t + 1] += __builtin_amdgcn_perm(0u, z, 0x0C030C01u);
-            }
+            if constexpr (DEG == 1) rj[t] = ((w | 0x80808080u) - q[t]) & w;
+            else rj[t] = w - q[t];
         }
         Rec<NR> Xn;
         if constexpr (D16) {
@@ -2001,6 +1996,23 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
             for (int t = 0; t < NR; ++t) Xc.v[t] = Xn.v[t] ^ ONE;
             rec_store<NR>(comp, Xc);
         }
+        // Counters and energy changes, while the store is on its way.
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < ND; ++t) {
+            const uint32_t w = wt[t], r = rj[t];
+            att_c += __builtin_popcount(w & real[t]);
+            acc_c += __builtin_popcount(w & ~r & real[t]);
+            if constexpr (D16) {
+                const uint32_t z = bit_select(__builtin_amdgcn_perm(0u, r, 0x09090808u), BIASW, w);
+                acc[t] += z & 0xFFFFu;
+                acc[t + 2] += z >> 16;
+            } else {
+                const uint32_t z = bit_select(__builtin_amdgcn_perm(r << 8, r, 0x090B080Au), BIASW, w);
+                acc[2 * t] += z & 0x00FF00FFu;
+                acc[2 * t + 1] += __builtin_amdgcn_perm(0u, z, 0x0C030C01u);
+            }
+        }
         if (++items_done == 64) flush((int)(s & 1u));
     };
     // Draw for 64 slots from `slot` on (padding slots draw for node 0).
@@ -2011,15 +2023,21 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     };
 
     // The wave's item stream: while an item is worked on, the next item's
-    // block and the header of the third item ahead are on their way. Items go
-    // in pairs with the two block buffers' roles swapped (the host pads the
-    // sweep to an even count), so no registers are copied. Every step issues
-    // the same vector loads -- rows an item does not have are read from what
-    // follows its block and ignored -- so the wait for a block counts the
+    // block and the header of the third item ahead are on their way. They are
+    // asked for behind the item's own LDS reads, whose latency covers the
+    // instructions (n = 800, degree 10: 108.5 -> 101.6 us a launch; asked for
+    // when needed only, 142: a block comes from L2 in the time of an item).
+    // Items go in pairs with the two block buffers' roles swapped (the host
+    // pads the sweep to an even count), so no registers are copied. Every step
+    // issues the same vector loads -- rows an item does not have are read from
+    // what follows its block and ignored -- so the wait for a block counts the
     // loads behind it and leaves them in flight; headers come through vector
     // loads too, because a scalar load would share the LDS counter and every
-    // wait for a record would wait for it.
-    constexpr int ROWS = FUSE ? 1 : 3;
+    // wait for a record would wait for it. A row costs a compute unit 16
+    // cycles of load return whether it is used or not, hence two rows and more
+    // lanes per node rather than three (signed n = 2,000, degree 20: 285 ->
+    // 250 us; n = 7,000, degree 12: 392 -> 367); only the 16-bit counters have
+    // nodes whose row needs a third.
     TileBlk bA, bB;
     const __amdgpu_buffer_rsrc_t brs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(blocks), 0, 0x7FFFFFF0, 0x00027000);
@@ -2047,7 +2065,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
         b.r0 = get(h.x);
         if constexpr (ROWS > 1) {
             b.r1 = get(h.x + step);
-            b.r2 = get(h.x + step + step);
+            if constexpr (ROWS > 2) b.r2 = get(h.x + step + step);
         }
     };
     // Halves of the draw buffer: decided from qa, drawn into qa + qx.
@@ -2065,21 +2083,27 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     int2 hv = head();
     fetch(bA, h0);
     auto step = [&](TileBlk &cur, TileBlk &nxt, uint32_t s) {
-        const int2 h3 = head();
-        fetch(nxt, h1);
         const uint32_t x = (uint32_t)h0.y;
         const uint32_t kind = x & kItemKind;
+        int2 h3;
+        auto next = [&]() {
+            h3 = head();
+            fetch(nxt, h1);
+        };
         if (kind == (1u << 28)) {
             if constexpr (FUSE) {
-                decide_even(cur, s);
+                decide_even(cur, s, next);
                 ++items_done;
             } else {
-                decide(cur, x, s, qa);
+                decide(cur, x, s, qa, next);
             }
-        } else if (!FUSE && kind != 0u) {
-            // 2: of this sweep, 3: of the next (none after the last).
-            const uint32_t s2 = s + (kind == kItemKind ? 1u : 0u);
-            if (s2 < (uint32_t)a.S) produce(cur.r0.x, item_slot(x), s2, qa + (uint32_t)qx);
+        } else {
+            next();
+            if (!FUSE && kind != 0u) {
+                // 2: of this sweep, 3: of the next (none after the last).
+                const uint32_t s2 = s + (kind == kItemKind ? 1u : 0u);
+                if (s2 < (uint32_t)a.S) produce(cur.r0.x, item_slot(x), s2, qa + (uint32_t)qx);
+            }
         }
         if (x & (1u << 30)) __syncthreads();
         if (!FUSE && (int)x < 0) {                  // the next chunk: change halves

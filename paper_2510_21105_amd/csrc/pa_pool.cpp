@@ -251,7 +251,7 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     tile.deg = degree_class(s->dmax);
     tile.byte_W = byte.W;
     tile.byte_threads = byte.threads;
-    if (s->dmax <= kMaxBytesDegree && shared_tile_form(s, plan.n_levels, p->max_lds, &tile.fuse)) {
+    if (s->dmax <= kMaxBytesDegree && shared_tile_form(s, plan.n_levels, &tile.fuse)) {
         if (tile.fuse) tile.bsg = 2;
         const int fit = p->max_lds / tile.lds(s->n, s->dmax);
         tile.threads = fit < 1 ? 1024 : tile_threads(1 << 16, tile.lds(s->n, s->dmax), p->max_lds,
