@@ -2517,14 +2517,20 @@ __device__ __forceinline__ void epilogue_body(const EpiArgs &a)
             const uint64_t u = __umul64hi(U, S);
             // f(c) counts the sampling points u + j S below R c: one division
             // for this thread's first replica, then walk the points (each step
-            // is one copy written), so no division per replica.
+            // is one copy written), so no division per replica. Far from
+            // equilibrium a few replicas take most of the copies: a replica
+            // with more than kWalk has the rest counted by a division and
+            // written by its whole wave, not by one lane in turn (140 x 140
+            // torus, 100 steps, R = 8,192: 41 -> 18 us a launch).
+            constexpr int kWalk = 4;
             uint64_t f = sys_f(excl, (uint64_t)R, u, S);
             uint64_t pt = u + f * S;                    // next sampling point
             uint64_t RC = (uint64_t)R * excl;
             long long parents = 0;
-            for (int r0 = lo; r0 < hi; r0 += CH) {
+            for (int q = 0; q < per; q += CH) {         // (the same count in every lane)
+                const int r0 = lo + q;
                 uint64_t wv[CH];
-                if (r0 == lo) {
+                if (q == 0) {
 #pragma unroll
                     for (int c = 0; c < CH; ++c) wv[c] = w0[c];
                 } else {
@@ -2533,15 +2539,29 @@ __device__ __forceinline__ void epilogue_body(const EpiArgs &a)
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
                     const int r = r0 + c;
-                    if (r >= hi) break;
-                    RC += (uint64_t)R * wv[c];
+                    const bool have = r < hi;
                     const uint64_t f0 = f;
-                    while (pt < RC) {
+                    if (have) RC += (uint64_t)R * wv[c];
+                    for (int t = 0; t < kWalk && have && pt < RC; ++t) {
                         a.parent[f] = r;
                         ++f;
                         pt += S;
                     }
-                    if (a.counts_rec) a.counts_rec[(size_t)a.k * R + r] = (int)(f - f0);
+                    const bool many = have && pt < RC;
+                    unsigned long long heavy = __ballot(many);
+                    if (heavy) {
+                        const int more = many ? (int)((RC - pt + S - 1) / S) : 0, from = (int)f;
+                        f += (uint64_t)more;
+                        pt += (uint64_t)more * S;
+                        for (; heavy; heavy &= heavy - 1) {
+                            const int l = (int)__builtin_ctzll(heavy);
+                            const int cnt = __builtin_amdgcn_readlane(more, l);
+                            const int at = __builtin_amdgcn_readlane(from, l);
+                            const int who = __builtin_amdgcn_readlane(r, l);
+                            for (int t = lane; t < cnt; t += 64) a.parent[at + t] = who;
+                        }
+                    }
+                    if (a.counts_rec && have) a.counts_rec[(size_t)a.k * R + r] = (int)(f - f0);
                     parents += f > f0;
                 }
             }
@@ -3302,6 +3322,15 @@ int launch_sweep_multi(const MultiShape &sh, const MultiRun *runs, const int2 *w
     }
 }
 
+// Threads of a step's epilogue: its chain of barriers is shorter with fewer
+// waves (R = 128: 52.5 us a whole step of 10 sweeps on 20 nodes with 1,024
+// threads, 49.4 with 128; R = 4,096, n = 7,000: 400 and 398 with 512), its loops
+// with more (R = 16,384: 621 with 512, 609). Adaptive steps try a jump a wave.
+static int epilogue_threads(int R, bool adapt)
+{
+    return R <= 512 && !adapt ? 128 : R <= 8192 ? 512 : kMaxThreads;
+}
+
 int launch_epilogue_multi(int runs_count, int max_R, const MultiRun *runs, int k, void *stream)
 {
     const int lds = max_R * 4;
@@ -3309,8 +3338,8 @@ int launch_epilogue_multi(int runs_count, int max_R, const MultiRun *runs, int k
     if (allow_lds(reinterpret_cast<const void *>(&epilogue_multi_kernel), configured, lds,
                   "hipFuncSetAttribute(epilogue_multi)"))
         return -1;
-    hipLaunchKernelGGL(epilogue_multi_kernel, dim3(runs_count), dim3(kMaxThreads), lds, (hipStream_t)stream,
-                       runs, k);
+    hipLaunchKernelGGL(epilogue_multi_kernel, dim3(runs_count), dim3(epilogue_threads(max_R, false)), lds,
+                       (hipStream_t)stream, runs, k);
     return check("epilogue_multi_kernel");
 }
 
@@ -3321,7 +3350,8 @@ int launch_epilogue(const EpiArgs &a, void *stream)
     if (allow_lds(reinterpret_cast<const void *>(&epilogue_kernel), configured, lds,
                   "hipFuncSetAttribute(epilogue)"))
         return -1;
-    hipLaunchKernelGGL(epilogue_kernel, dim3(1), dim3(kMaxThreads), lds, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(epilogue_kernel, dim3(1), dim3(epilogue_threads(a.R, a.adapt != 0)), lds,
+                       (hipStream_t)stream, a);
     return check("epilogue_kernel");
 }
 
