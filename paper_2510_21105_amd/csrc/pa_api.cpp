@@ -746,14 +746,6 @@ int pa_host::tile_threads(int need, int lds, int max_lds, long long per_level, i
     return fit == 2 ? 768 : 512;
 }
 
-// Whether a run that shares launches can take the tile form (many generations
-// of workgroups, where it is the faster one: see take_tile_form).
-bool pa_host::shared_tile_form(const pa_solver *s, int n_levels, int *fuse)
-{
-    *fuse = fuse_draws(s, n_levels);
-    return !s->has_neg || s->n + 256 <= 0x7FFF;
-}
-
 // Whether a run takes the tile form, and its shape then; p comes with the
 // general form's choice and the levels. All figures: one step of 10 sweeps on
 // MI355X, microseconds.

@@ -123,13 +123,8 @@ int pa_host::device_max_lds()
 
 namespace {
 
-// Tile widths the autotuner tries, each with 64, 128, 256 and 512 threads.
+// Tile widths the autotuner tries, each with 256, 512 and 1,024 threads.
 constexpr int kTileCand[] = {4, 8, 16};
-
-bool direct_fits(const pa_solver *s, int W)
-{
-    return pa::kBytesRecBase + (size_t)(s->n + 1) * W <= 0xFFFF;
-}
 
 // Plan a run with a shape without tables (sizes only).
 pa_status plan_size(pa_fused::Run &r, const Shape &sh, size_t *bytes)
@@ -324,18 +319,18 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
     if (std::adjacent_find(seen.begin(), seen.end()) != seen.end())
         return bail(fail(PA_EINVAL, "pa_fused_create: a solver appears in two runs"));
 
-    // Threads per workgroup of each run for the untuned shape: the smallest
-    // of 64, 128, 256, 512 that needs no more rounds (one barrier each) per
-    // sweep than 512; a round covers one dependency level, and graphs of a
-    // few thousand nodes have levels of 50 to 300 nodes.
-    std::vector<int> threads(count, 512), fuse(count, 0), tiled(count, 0), levels(count, 1);
+    // Every run is planned once with the narrowest tile (what a shared launch
+    // refuses is refused here), for its levels.
+    std::vector<int> fuse(count, 0), levels(count, 1);
     for (int i = 0; i < count; ++i) {
         pa_fused::Run &r = f->runs[i];
         Shape probe;
         probe.W = 4;
         probe.threads = 512;
         probe.bsg = r.s->has_neg ? 2 : 0;
+        probe.ahead = 1;
         probe.direct = 0;
+        probe.deg = degree_class(r.s->dmax);
         Plan p;
         pa_status st = build_plan(r.s, &r.sch, r.R, p, false, &probe);
         if (st != PA_OK) {
@@ -343,16 +338,8 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
             std::snprintf(msg, sizeof msg, "%s", pa_last_error());
             return bail(fail(st, "pa_fused_create: run %d: %s", i, msg));
         }
-        auto rounds_at = [&](int T) {
-            long long n = 0;
-            for (int l = 0; l < p.n_levels; ++l) n += (p.level_off[l + 1] - p.level_off[l] + T - 1) / T;
-            return n;
-        };
-        const long long r512 = rounds_at(512);
-        for (int T : {256, 128, 64})
-            if (rounds_at(T) <= r512) threads[i] = T;
         levels[i] = p.n_levels;
-        tiled[i] = shared_tile_form(r.s, p.n_levels, &fuse[i]);
+        fuse[i] = fuse_draws(r.s, p.n_levels);
     }
     int cus = 256, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -373,50 +360,41 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
         for (int sc = 3; sc >= 0; --sc) {
         pa_fused::Group g;
         g.bsg = bsg;
-        int T0 = 64, deg = 0, all_fuse = 1;
-        double for_tile = 0, nodes = 0, lvls = 0;
+        int T0 = 512, deg = 0, all_fuse = 1;
+        double nodes = 0, lvls = 0;
         for (int i = 0; i < count; ++i)
             if ((f->runs[i].s->has_neg ? 2 : 0) == bsg && size_class(f->runs[i].s->n) == sc) {
                 g.members.push_back(i);
-                T0 = std::max(T0, threads[i]);
                 deg = std::max(deg, degree_class(f->runs[i].s->dmax));
                 all_fuse &= fuse[i];
-                for_tile += (tiled[i] ? 1 : -1) * f->runs[i].cost * f->runs[i].R;
                 nodes += f->runs[i].s->n;
                 lvls += levels[i];
             }
         if (g.members.empty()) continue;
         std::stable_sort(g.members.begin(), g.members.end(),
                          [&](int a, int b) { return f->runs[a].cost > f->runs[b].cost; });
-        // The form that suits most of the group's work; the tile form takes
-        // its threads from what is resident (tile_threads), the byte form
-        // from the levels.
-        const int ahead = for_tile > 0;
         const long long per_level = (long long)(nodes / lvls);
-        int want = ahead && tiles4 <= cus ? 4 : 8;
+        const int want = tiles4 <= cus ? 4 : 8;
         for (int W : kTileCand)
-            for (int T : {64, 128, 256, 512, 768, 1024}) {
-                if (ahead ? T < 256 : T > 512) continue;
+            for (int T : {256, 512, 1024}) {
                 Shape sh;
                 sh.W = W;
                 sh.threads = T;
                 sh.bsg = bsg;
-                sh.ahead = ahead;
-                sh.direct = !ahead;
-                sh.deg = ahead ? deg : 0;
-                sh.fuse = ahead && W <= 8 && bsg == 2 && all_fuse;
-                bool ok = true;
+                sh.ahead = 1;
+                sh.direct = 0;
+                sh.deg = deg;
+                sh.fuse = W <= 8 && bsg == 2 && all_fuse;
                 int lds = 0;
-                for (int i : g.members) {
-                    const pa_solver *s = f->runs[i].s;
-                    lds = std::max(lds, sh.lds(s->n, s->dmax));
-                    if (!ahead && !direct_fits(s, W)) sh.direct = 0;
-                }
-                if (lds > f->max_lds) ok = false;
-                if (ok && ahead && W == want)
+                for (int i : g.members) lds = std::max(lds, sh.lds(f->runs[i].s->n, f->runs[i].s->dmax));
+                if (lds > f->max_lds) continue;
+                // (768, where one group alone would take it, is two workgroups
+                // a compute unit: 512 leaves room for another group's.)
+                if (W == want)
                     T0 = tile_threads((int)(((W == 4 ? tiles4 : tiles8) + cus - 1) / cus), lds, f->max_lds, per_level,
                                       sh.fuse);
-                if (ok) g.candidates.push_back(sh);
+                if (T0 == 768) T0 = 512;
+                g.candidates.push_back(sh);
             }
         if (g.candidates.empty())
             return bail(fail(PA_ERANGE, "pa_fused_create: a graph does not fit LDS at any shared shape"));

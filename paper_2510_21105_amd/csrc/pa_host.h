@@ -99,9 +99,6 @@ struct Shape {
 };
 // The sweep order's dependency levels (Plan::n_levels, level_off, sched).
 void build_levels(const pa_solver *s, const int32_t *order, Plan &p);
-// Whether a run that shares launches takes the tile form, and whether that form
-// draws in registers then.
-bool shared_tile_form(const pa_solver *s, int n_levels, int *fuse);
 // Threads of a tile-form workgroup of `lds` bytes where `need` of them come to
 // a compute unit.
 int tile_threads(int need, int lds, int max_lds, long long per_level, int fuse);

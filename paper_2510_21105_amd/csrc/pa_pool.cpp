@@ -220,13 +220,13 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     j.seed = run->seed;
     j.inst = run->instance;
     j.K = run->schedule->n_steps;
-    // Shape: 8 replicas per workgroup where a tile's records fit LDS, else 4;
-    // sign-bit entries for graphs with -1 weights. The form of
-    // shared_tile_form, with the threads of a busy compute unit (as many
-    // workgroups as its LDS holds); in the byte form LDS offsets as entries
-    // where they fit 16 bits, and the smallest of 64, 128, 256, 512 threads
-    // whose rounds per sweep (one per dependency-level chunk) are no more
-    // than with 512.
+    // Shape: 8 replicas per workgroup in the tile form, with the threads of a
+    // busy compute unit (as many workgroups as its LDS holds); sign-bit entries
+    // for graphs with -1 weights. Where the pool is too small for that form's
+    // plan, the byte form: 8 replicas where a tile's records fit LDS, else 4,
+    // LDS offsets as entries where they fit 16 bits, and the smallest of 64,
+    // 128, 256, 512 threads whose rounds per sweep (one per dependency-level
+    // chunk) are no more than with 512.
     const pa_solver *s = run->solver;
     Shape byte;
     byte.bsg = s->has_neg ? 2 : 0;
@@ -243,7 +243,6 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     const long long r512 = rounds_at(512);
     for (int T : {256, 128, 64})
         if (rounds_at(T) <= r512) byte.threads = T;
-    j.shape = byte;
     Shape tile = byte;
     tile.ahead = 1;
     tile.W = 8;
@@ -251,13 +250,10 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     tile.deg = degree_class(s->dmax);
     tile.byte_W = byte.W;
     tile.byte_threads = byte.threads;
-    if (s->dmax <= kMaxBytesDegree && shared_tile_form(s, plan.n_levels, &tile.fuse)) {
-        if (tile.fuse) tile.bsg = 2;
-        const int fit = p->max_lds / tile.lds(s->n, s->dmax);
-        tile.threads = fit < 1 ? 1024 : tile_threads(1 << 16, tile.lds(s->n, s->dmax), p->max_lds,
-                                                     s->n / plan.n_levels, tile.fuse);
-        if (fit >= 1) j.shape = tile;
-    }
+    tile.fuse = fuse_draws(s, plan.n_levels);
+    if (tile.fuse) tile.bsg = 2;
+    tile.threads = tile_threads(1 << 16, tile.lds(s->n, s->dmax), p->max_lds, s->n / plan.n_levels, tile.fuse);
+    j.shape = tile;
     plan = Plan();
     st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape);
     if (st == PA_OK && j.shape.ahead && align_up(plan.L.total) > p->bytes - p->heap_off) {
