@@ -61,9 +61,10 @@ typedef struct {
     double as_gamma;          /* level l sweeps at beta_k * gamma^l, 0 < gamma <= 1 */
     int32_t nl_period;        /* non-local cluster moves every nl_period steps, 0 = off;
                                  the kind is nl_kind below                       */
-    int32_t sweep_kernel;     /* 0 = automatic; 1 = one node per lane over byte spin
-                                 records (max degree <= 127); 2 = one replica per lane
-                                 over bit spin words. Results never depend on it.  */
+    int32_t sweep_kernel;     /* 0 = automatic; 1 = nodes over lanes, spins as byte or
+                                 nibble records (max degree <= 127; chosen automatically
+                                 up to 1023); 2 = one replica per lane over bit spin
+                                 words. Results never depend on it.                */
     int32_t tile_replicas;    /* replicas per workgroup, 0 = automatic; kernel 1 takes
                                  4, 8 or 16, kernel 2 takes 16, 32 or 64. Results
                                  never depend on it.                              */
