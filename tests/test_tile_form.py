@@ -104,3 +104,39 @@ def test_shared_launches(pa):  # noqa: F811
     fb.run()
     for w, p, s in zip(wls, params, solvers):
         _check_against_oracle(s, w, p)
+
+
+def test_pool_without_room_for_the_tile_plan(pa):  # noqa: F811
+    """The smallest pool that takes a run steps it in the general form."""
+    import torch
+    L = 20
+    g = W.torus(L, 3, True)
+    wl = dict(W.workload("torus100"), graph=g, R=40, betas=[0.2, 0.9, 2.0], sweeps=2, order=W.natural_order(g.n))
+    p = pa.params_from_workload(wl)
+    s, t = pa.Solver(g), pa.Solver(g)
+    s.run(p)
+    mem = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+
+    def takes(size):
+        try:
+            pool = pa.Pool(workspace=(mem.data_ptr(), size))
+            pool.submit(t, p)
+        except pa.PAError:
+            return None
+        return pool
+
+    lo, hi = 1, (64 << 20) // 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if takes(256 * mid) else (mid, hi)
+    for size, general in ((256 * hi, True), (64 << 20, False)):
+        pool = takes(size)
+        while not pool.advance(iterations=8):
+            pass
+        torch.cuda.synchronize()
+        assert len(pool.poll()) == 1
+        assert (t.launch_info()["lds_bytes"] < 16384) == general
+        for a, b in zip(s.population(), t.population()):
+            assert np.array_equal(a, b)
+        assert np.array_equal(s.step_stats(), t.step_stats()) and s.best_info() == t.best_info()
+        pool.close()
