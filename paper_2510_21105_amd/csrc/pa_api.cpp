@@ -230,38 +230,46 @@ pa_status pa_host::check_schedule(const pa_solver *s, const pa_schedule *sch, in
 // neighbours visited before i (0 if none). Nodes of one level are pairwise
 // non-adjacent, and visiting levels in increasing order reproduces the
 // sequential sweep exactly, since each attempt only reads its neighbours.
-void pa_host::build_levels(const pa_solver *s, const int32_t *order, Plan &p)
+void pa_host::build_levels(const pa_solver *s, const int32_t *order, Levels &p)
 {
     const int n = s->n;
-    std::vector<int> pos(n), lvl(n, 0);
-    for (int t = 0; t < n; ++t) pos[order ? order[t] : t] = t;
+    const int *row_ptr = s->row_ptr.data(), *col = s->col.data();
+    std::vector<int> lvl(n, -1);                // -1: not visited yet
+    std::vector<int> by_degree(s->dmax + 2, 0);
     int nl = 0;
     for (int t = 0; t < n; ++t) {
         const int i = order ? order[t] : t;
-        int l = 0;
-        for (int e = s->row_ptr[i]; e < s->row_ptr[i + 1]; ++e) {
-            const int j = s->col[e];
-            if (pos[j] < t) l = std::max(l, lvl[j] + 1);
+        int l = -1, l1 = -1, l2 = -1, l3 = -1;  // (four maxima: long rows wait for no chain)
+        int e = row_ptr[i];
+        for (; e + 4 <= row_ptr[i + 1]; e += 4) {
+            l = std::max(l, lvl[col[e]]);
+            l1 = std::max(l1, lvl[col[e + 1]]);
+            l2 = std::max(l2, lvl[col[e + 2]]);
+            l3 = std::max(l3, lvl[col[e + 3]]);
         }
+        for (; e < row_ptr[i + 1]; ++e) l = std::max(l, lvl[col[e]]);
+        l = std::max(std::max(l, l1), std::max(l2, l3)) + 1;
         lvl[i] = l;
         nl = std::max(nl, l + 1);
+        ++by_degree[s->dmax - (row_ptr[i + 1] - row_ptr[i]) + 1];
     }
     p.n_levels = nl;
     p.level_off.assign(nl + 1, 0);
     for (int i = 0; i < n; ++i) p.level_off[lvl[i] + 1]++;
     for (int l = 0; l < nl; ++l) p.level_off[l + 1] += p.level_off[l];
-    std::vector<int> fill(p.level_off.begin(), p.level_off.end() - 1);
-    p.sched.assign(n, 0);
-    for (int t = 0; t < n; ++t) {
-        const int i = order ? order[t] : t;
-        p.sched[fill[lvl[i]]++] = i;
-    }
     // Within a level the visiting order is free; grouping equal degrees
     // keeps the slots of one pass (which loop to their largest degree) even.
-    auto deg = [&](int i) { return s->row_ptr[i + 1] - s->row_ptr[i]; };
-    for (int l = 0; l < nl; ++l)
-        std::stable_sort(p.sched.begin() + p.level_off[l], p.sched.begin() + p.level_off[l + 1],
-                         [&](int x, int y) { return deg(x) > deg(y); });
+    // The nodes by falling degree first (visiting order among equals), then
+    // dealt to their levels in that order.
+    for (int d = 0; d < s->dmax; ++d) by_degree[d + 1] += by_degree[d];
+    std::vector<int> nodes(n);
+    for (int t = 0; t < n; ++t) {
+        const int i = order ? order[t] : t;
+        nodes[by_degree[s->dmax - (row_ptr[i + 1] - row_ptr[i])]++] = i;
+    }
+    std::vector<int> fill(p.level_off.begin(), p.level_off.end() - 1);
+    p.sched.assign(n, 0);
+    for (int i : nodes) p.sched[fill[lvl[i]]++] = i;
 }
 
 // Adjacency blocks in schedule order, one fixed-size block per slot:
@@ -390,6 +398,13 @@ static void build_blocks(const pa_solver *s, Plan &p, int direct)
         }
 }
 
+// Parts of at most `most` that `count` >= 1 is cut into. (One, in most levels:
+// no division then.)
+static inline int parts(int count, int most)
+{
+    return count <= most ? 1 : (count + most - 1) / most;
+}
+
 bool pa_host::fuse_draws(const pa_solver *s, int n_levels)
 {
     return (s->dmax == 4 || s->dmax == 2) && s->nnz == (long long)s->n * s->dmax && s->n + 256 <= 0x7FFF &&
@@ -400,15 +415,12 @@ bool pa_host::fuse_draws(const pa_solver *s, int n_levels)
 // sweep_tile_kernel). Every level is cut into items of at most 64 lanes, dealt over the
 // waves; levels are gathered into chunks whose draws fit half the draw buffer,
 // and the draws of a chunk are dealt, as items of 64 slots, into the places
-// that the chunk before it leaves free.
-static void build_tile_plan(const pa_solver *s, Plan &p)
+// that the chunk before it leaves free. Without `fill` only the sizes are set:
+// they follow from the cut and from where the draws go, and no row is written.
+static void build_tile_plan(const pa_solver *s, Plan &p, bool fill)
 {
     const int n = s->n, W = p.W, nw = p.threads / 64;
     const bool d16 = p.deg == 2;
-    auto degree = [&](int slot) {
-        const int i = p.sched[slot];
-        return s->row_ptr[i + 1] - s->row_ptr[i];
-    };
     // Entries a lane's block holds: 6 + 8 after a short header, 4 in the first
     // row after a long one, 8 more with 16-bit counters (16 in all with sign
     // bits), four with draws in registers. A node of a larger degree takes
@@ -419,27 +431,29 @@ static void build_tile_plan(const pa_solver *s, Plan &p)
     const int e0 = long_head ? 4 : 6;
     const int most = p.fuse ? e0 : !d16 ? e0 + 8 : p.bsg == 2 ? 16 : e0 + 16, lp_max = d16 ? 6 : 4;
     struct Item {
-        int slot, count, lp, rows;
+        int slot, count, lp, rows, per;     // per: entries a lane, of the largest node
+        int lanes() const { return count << lp; }
     };
     std::vector<Item> cut;
+    cut.reserve(p.n_levels + n / 32);
     std::vector<int> level_item(p.n_levels + 1, 0);
     for (int l = 0; l < p.n_levels; ++l) {
         for (int t = p.level_off[l]; t < p.level_off[l + 1];) {
-            const int md = degree(t);
+            const int i = p.sched[t], md = s->row_ptr[i + 1] - s->row_ptr[i];
             auto per_lane = [&](int lp) { return (md + (1 << lp) - 1) >> lp; };
-            Item it{t, 0, 0, 1};
+            Item it{t, 0, 0, 1, 0};
             while (per_lane(it.lp) > most) ++it.lp;
             it.count = std::min(p.level_off[l + 1] - t, 64 >> it.lp);
             while (it.lp < lp_max && per_lane(it.lp) > e0 && it.count << (it.lp + 1) <= 64) ++it.lp;
-            const int e = per_lane(it.lp);
-            it.rows = e <= e0 ? 1 : 1 + (e - e0 + 7) / 8;
+            it.per = per_lane(it.lp);
+            it.rows = it.per <= e0 ? 1 : 1 + (it.per - e0 + 7) / 8;
             cut.push_back(it);
             t += it.count;
         }
         level_item[l + 1] = (int)cut.size();
     }
     p.n_rounds = 0;
-    for (int l = 0; l < p.n_levels; ++l) p.n_rounds += (level_item[l + 1] - level_item[l] + nw - 1) / nw;
+    for (int l = 0; l < p.n_levels; ++l) p.n_rounds += parts(level_item[l + 1] - level_item[l], nw);
 
     // Chunks: runs of items whose slots fit a half of the draw buffer.
     const int cap = pa::tile_draw_slots(W, d16) / 128 * 64;
@@ -465,10 +479,11 @@ static void build_tile_plan(const pa_solver *s, Plan &p)
                 ++c;
                 k = 0;
             }
-            item_wave[q] = k++ % nw;
+            item_wave[q] = k;
+            k = k + 1 < nw ? k + 1 : 0;
         }
 
-    // Blocks: the draw items' nodes, then the levels' rows.
+    // Places of the blocks: the draw items' nodes, then the levels' rows.
     const int rec_words = 8;            // u16 per lane and row
     std::vector<int> draw_at(n_chunks, 0);      // uint4 offset of a chunk's draw blocks
     std::vector<int> draw_items(n_chunks, 0);
@@ -482,157 +497,204 @@ static void build_tile_plan(const pa_solver *s, Plan &p)
     std::vector<int> block_at(cut.size());
     for (size_t c = 0; c < cut.size(); ++c) {
         block_at[c] = (int)u4;
-        u4 += (size_t)cut[c].rows * ((cut[c].count << cut[c].lp) + 1);
+        u4 += (size_t)cut[c].rows * (cut[c].lanes() + 1);
     }
     u4 += 2 * 65;                               // rows that the last items do not have
-    std::vector<uint16_t> b16(u4 * rec_words, 0);
-    for (int c = 0; c < (p.fuse ? 0 : n_chunks); ++c)
-        for (int t = 0; t < 64 * draw_items[c]; ++t) {
-            uint16_t *b = &b16[((size_t)draw_at[c] + t) * rec_words];
-            const int slot = chunk_slot(c) + t;
-            b[0] = slot < chunk_slot(c + 1) ? (uint16_t)p.sched[slot] : 0;
+    p.row_bytes = u4 * sizeof(uint16_t) * rec_words;
+
+    // Streams. An interval runs from barrier to barrier: a level, or a run of
+    // levels that wave 0 takes by itself. Its items are cut[q0 .. q1).
+    struct Interval {
+        int q0, q1;
+        int longest;                            // items of its longest wave
+        int wave;                               // where one more draw lengthens it least
+        long long cost;                         //   and by how much (2^32: it does)
+    };
+    struct Draw {
+        int iv, wave, t;
+    };
+    std::vector<std::vector<int2>> st(fill ? nw : 0);
+    std::vector<int> st_len(nw, 0);
+    std::vector<Interval> iv;
+    std::vector<int> len;                       // items of each interval and wave
+    std::vector<Draw> placed;
+    const int2 nothing{0, pa::item_word(0, 0, 1, 0, 0)};
+    for (int c = 0, l = 0; c < n_chunks; ++c) {
+        iv.clear();
+        int wave0_run = 0;                      // the open interval is wave 0's alone
+        for (int q = chunk_item[c]; q < chunk_item[c + 1];) {
+            while (level_item[l + 1] <= q) ++l;
+            const int end = std::min(level_item[l + 1], chunk_item[c + 1]);
+            const int alone = solo || level_item[l + 1] - level_item[l] == 1;
+            if (iv.empty() || !(alone && wave0_run)) {
+                iv.push_back(Interval{q, q, 0, 0, 0});
+                wave0_run = alone;
+            }
+            iv.back().q1 = q = end;
         }
+        len.assign(iv.size() * nw, 0);
+        for (size_t v = 0; v < iv.size(); ++v)
+            for (int q = iv[v].q0; q < iv[v].q1; ++q) ++len[v * nw + item_wave[q]];
+        const int c2 = c + 1 < n_chunks ? c + 1 : 0;
+        placed.clear();
+        if (!p.fuse) {
+            // The next chunk's draws, each where it lengthens its interval
+            // least (wave 0 last).
+            auto offer = [&](size_t v) {
+                const int *m = &len[v * nw];
+                iv[v].longest = *std::max_element(m, m + nw);
+                iv[v].wave = -1;
+                for (int w = nw - 1; w >= 0; --w) {
+                    const long long more = (long long)m[w] + 1;
+                    const long long cost = more > iv[v].longest ? (1LL << 32) + more : more - iv[v].longest;
+                    if (iv[v].wave < 0 || cost < iv[v].cost) {
+                        iv[v].wave = w;
+                        iv[v].cost = cost;
+                    }
+                }
+            };
+            for (size_t v = 0; v < iv.size(); ++v) offer(v);
+            for (int t = 0; t < draw_items[c2]; ++t) {
+                size_t best = 0;
+                for (size_t v = 1; v < iv.size(); ++v)
+                    if (iv[v].cost < iv[best].cost) best = v;
+                placed.push_back(Draw{(int)best, iv[best].wave, t});
+                ++len[best * nw + iv[best].wave];
+                offer(best);
+            }
+            std::stable_sort(placed.begin(), placed.end(), [](const Draw &x, const Draw &y) { return x.iv < y.iv; });
+        }
+        const int kind = c + 1 < n_chunks ? 2 : 3;
+        for (size_t v = 0, d = 0; v < iv.size(); ++v) {
+            const bool chunk_end = v + 1 == iv.size(), sweep_end = chunk_end && c + 1 == n_chunks;
+            // (The sweep's last barrier is the kernel's own.)
+            const int flags = (sweep_end ? 0 : pa::kItemBarrier) | (chunk_end && !p.fuse ? pa::kItemChunk : 0);
+            for (int w = 0; w < nw; ++w) st_len[w] += flags != 0 && len[v * nw + w] == 0 ? 1 : len[v * nw + w];
+            if (!fill) continue;
+            for (int q = iv[v].q0; q < iv[v].q1; ++q) {
+                const Item &it = cut[q];
+                st[item_wave[q]].push_back(
+                    int2{block_at[q] * 16,
+                         pa::item_word(it.lanes(), p.fuse ? 0 : it.slot - chunk_slot(c), it.rows, it.lp, 1)});
+            }
+            for (; d < placed.size() && placed[d].iv == (int)v; ++d)
+                st[placed[d].wave].push_back(
+                    int2{(draw_at[c2] + 64 * placed[d].t) * 16, pa::item_word(63, 64 * placed[d].t, 1, 0, kind)});
+            for (int w = 0; w < nw && flags != 0; ++w) {
+                if (len[v * nw + w] == 0) st[w].push_back(nothing);
+                st[w].back().y |= pa::item_word(0, 0, 1, 0, flags);
+            }
+        }
+    }
+    // Every stream has an even count of items, and its first three again.
+    p.item_ints = 0;
+    p.streams.assign((size_t)4 * nw, 0);
+    for (int w = 0; w < nw; ++w) {
+        const int even = st_len[w] + (st_len[w] & 1);
+        int *head = &p.streams[(size_t)4 * w];
+        head[0] = (int)p.item_ints / 2;
+        head[1] = even;
+        head[2] = draw_at[0];
+        head[3] = draw_items[0];
+        p.item_ints += 2 * ((size_t)even + 3);
+    }
+    if (!fill) return;
+    p.items.clear();
+    p.items.reserve(p.item_ints);
+    for (std::vector<int2> &it : st) {
+        if (it.size() & 1) it.push_back(nothing);
+        const size_t m = it.size();
+        for (size_t q = 0; q < m + 3; ++q) {
+            const int2 v = m == 0 ? nothing : it[q % m];
+            p.items.push_back(v.x);
+            p.items.push_back(v.y);
+        }
+    }
+
+    // The blocks' contents.
+    const int rec0 = pa::tile_record(W, p.fuse, 0);     // record numbers follow one another
+    const int *sched = p.sched.data(), *row_ptr = s->row_ptr.data(), *col = s->col.data();
+    p.rows.assign(u4 * rec_words, 0);
+    uint16_t *const rows = p.rows.data();
+    for (int c = 0; c < (p.fuse ? 0 : n_chunks); ++c) {
+        uint16_t *b = rows + (size_t)draw_at[c] * rec_words;
+        for (int slot = chunk_slot(c); slot < chunk_slot(c + 1); ++slot, b += rec_words) b[0] = (uint16_t)sched[slot];
+    }
+    // A row is two words of four u16: a row of one record throughout, and the
+    // first k of four entries followed by `pad`.
+    auto all = [](int rec) { return 0x0001000100010001ull * (uint16_t)rec; };
+    auto put = [](uint16_t *b, uint64_t v) { std::memcpy(b, &v, sizeof v); };
+    auto four = [](const uint16_t *e, int k, uint64_t pad) {
+        if (k <= 0) return pad;
+        uint64_t v;
+        std::memcpy(&v, e, sizeof v);
+        const uint64_t past = k >= 4 ? 0 : ~0ull << 16 * k;
+        return (v & ~past) | (pad & past);
+    };
+    std::vector<uint16_t> entry(s->dmax + 8);   // a node's entries
+    const uint16_t neg_byte = W == 4 ? 0x01 : 0x11;
     for (size_t c = 0; c < cut.size(); ++c) {
         const Item &it = cut[c];
-        const int lanes = it.count << it.lp;
-        auto at = [&](int row, int lane) -> uint16_t * {
-            return &b16[((size_t)block_at[c] + (size_t)row * (lanes + 1) + lane) * rec_words];
-        };
-        const int dummy = pa::tile_record(W, p.fuse, (p.bsg == 1 ? 2 * n : n) + item_wave[c]);
-        for (int r = 0; r < it.rows; ++r)
-            for (int q = 0; q < rec_words; ++q) at(r, lanes)[q] = (uint16_t)dummy;
-        uint16_t *spare = at(0, lanes);
+        const int lanes = it.lanes();
+        const size_t stride = (size_t)(lanes + 1) * rec_words;
+        uint16_t *const block = rows + (size_t)block_at[c] * rec_words;
+        const int dummy = rec0 + (p.bsg == 1 ? 2 * n : n) + item_wave[c];
+        uint16_t *spare = block + (size_t)lanes * rec_words;
+        for (int r = 0; r < it.rows; ++r) {
+            put(spare + r * stride, all(dummy));
+            put(spare + r * stride + 4, all(dummy));
+        }
+        spare[1] = 0;
         // A FUSE block: {record, node}, a byte per neighbour where its edge is
         // negative, four neighbours. A dummy's first degree / 2 are.
-        const uint16_t neg_byte = W == 4 ? 0x01 : 0x11;
         if (p.fuse) {
-            spare[1] = 0;
             spare[2] = (uint16_t)(s->dmax == 4 ? neg_byte * 0x0101 : neg_byte);
             spare[3] = 0;
-            for (int lane = 0; lane < lanes; ++lane) {
-                const int i = p.sched[it.slot + lane], first = s->row_ptr[i];
-                uint16_t *h = at(0, lane);
-                for (int q = 0; q < rec_words; ++q) h[q] = (uint16_t)pa::tile_record(W, p.fuse, i);
-                h[1] = (uint16_t)i;
-                h[2] = h[3] = 0;
+            uint16_t *h = block;
+            for (int lane = 0; lane < lanes; ++lane, h += rec_words) {
+                const int i = sched[it.slot + lane];
+                const int *nb = col + row_ptr[i];
+                put(h, (uint16_t)(rec0 + i) | (uint64_t)i << 16);
+                put(h + 4, all(rec0 + i));
                 for (int q = 0; q < s->dmax; ++q) {
-                    h[4 + q] = (uint16_t)pa::tile_record(W, p.fuse, s->col[first + q]);
+                    h[4 + q] = (uint16_t)(rec0 + nb[q]);
                     if (q >= s->npos[i]) h[2 + q / 2] = (uint16_t)(h[2 + q / 2] | neg_byte << 8 * (q % 2));
                 }
             }
             continue;
         }
-        spare[1] = 0;
-        if (long_head) {
-            spare[2] = 0;
-            spare[3] = p.bsg == 1 ? (uint16_t)dummy : 0;
-        }
-        for (int lane = 0; lane < lanes; ++lane) {
-            const int i = p.sched[it.slot + (lane >> it.lp)], part = lane & ((1 << it.lp) - 1);
-            const int first = s->row_ptr[i], d = s->row_ptr[i + 1] - first;
-            const int per = (degree(it.slot) + (1 << it.lp) - 1) >> it.lp;
-            const int own = pa::tile_record(W, p.fuse, i);
-            for (int r = 0; r < it.rows; ++r)
-                for (int q = 0; q < rec_words; ++q) at(r, lane)[q] = (uint16_t)own;
-            uint16_t *h = at(0, lane);
-            h[1] = (uint16_t)d;
-            if (long_head) {
-                h[2] = (uint16_t)i;
-                h[3] = p.bsg == 1 ? (uint16_t)pa::tile_record(W, p.fuse, n + i) : 0;
-            }
-            for (int q = part * per; q < std::min(d, (part + 1) * per); ++q) {
-                const int t = q - part * per;
-                const int j = s->col[first + q];
-                const bool neg = q >= s->npos[i];
-                const uint16_t rec =
-                    (uint16_t)pa::tile_record(W, p.fuse, p.bsg == 1 && neg ? n + j : j);
-                // (A short header's third and fourth u16 are its entries 4 and 5.)
-                if (t < 4) h[4 + t] = rec;
-                else if (t < e0) h[t - 2] = rec;
-                else at(1 + (t - e0) / 8, lane)[(t - e0) % 8] = rec;
-                if (p.bsg == 2 && neg) h[3] = (uint16_t)(h[3] | 1u << t);
-            }
-        }
-    }
-    p.blocks.assign(b16.size() / 2, 0u);
-    std::memcpy(p.blocks.data(), b16.data(), b16.size() * sizeof(uint16_t));
-    p.block_bytes = 16;
-
-    // Streams. An interval runs from barrier to barrier: a level, or a run of
-    // levels that wave 0 takes by itself.
-    struct Interval {
-        std::vector<std::vector<int2>> wave;    // items of each wave
-    };
-    std::vector<std::vector<int2>> st(nw);
-    std::vector<Interval> iv;
-    int wave0_run = 0;                          // the open interval is wave 0's alone
-    auto open_interval = [&](int alone) {
-        iv.push_back(Interval{std::vector<std::vector<int2>>(nw)});
-        wave0_run = alone;
-    };
-    auto size_of = [&](const Interval &v) {
-        size_t m = 0;
-        for (const auto &w : v.wave) m = std::max(m, w.size());
-        return m;
-    };
-    for (int c = 0, l = 0; c < n_chunks; ++c) {
-        iv.clear();
-        for (int q = chunk_item[c]; q < chunk_item[c + 1];) {
-            while (level_item[l + 1] <= q) ++l;
-            const int end = std::min(level_item[l + 1], chunk_item[c + 1]);
-            const int alone = solo || level_item[l + 1] - level_item[l] == 1;
-            if (iv.empty() || !(alone && wave0_run)) open_interval(alone);
-            for (; q < end; ++q) {
-                const Item &it = cut[q];
-                iv.back().wave[item_wave[q]].push_back(
-                    int2{block_at[q] * 16, pa::item_word(it.count << it.lp, p.fuse ? 0 : it.slot - chunk_slot(c),
-                                                         it.rows, it.lp, 1)});
-            }
-        }
-        if (!p.fuse) {
-            // The next chunk's draws, each where it lengthens its interval
-            // least (wave 0 last).
-            const int c2 = c + 1 < n_chunks ? c + 1 : 0, kind = c + 1 < n_chunks ? 2 : 3;
-            for (int t = 0; t < draw_items[c2]; ++t) {
-                std::vector<int2> *best = nullptr;
-                long long best_cost = 0;
-                for (Interval &v : iv) {
-                    const long long longest = (long long)size_of(v);
-                    for (int w = nw - 1; w >= 0; --w) {
-                        const long long len = (long long)v.wave[w].size() + 1;
-                        const long long cost = len > longest ? (1LL << 32) + len : len - longest;
-                        if (!best || cost < best_cost) {
-                            best = &v.wave[w];
-                            best_cost = cost;
-                        }
-                    }
+        if (long_head) spare[3] = p.bsg == 1 ? (uint16_t)dummy : 0;
+        const int comp = p.bsg == 1 ? n : 0;
+        uint16_t *h = block;
+        for (int g = 0; g < it.count; ++g) {
+            const int i = sched[it.slot + g], d = row_ptr[i + 1] - row_ptr[i], own = rec0 + i;
+            const uint64_t pad = all(own);
+            const int *nb = col + row_ptr[i];
+            for (int t = 0; t < d; ++t) entry[t] = (uint16_t)(rec0 + nb[t]);
+            for (int t = s->npos[i]; t < d && comp != 0; ++t) entry[t] = (uint16_t)(entry[t] + comp);
+            for (int part = 0; part < 1 << it.lp; ++part, h += rec_words) {
+                // Entries q0 .. q0 + m - 1 of the row, the first `pos` of them positive.
+                const int q0 = std::min(d, part * it.per), m = std::min(d - q0, it.per);
+                const uint16_t *e = entry.data() + q0;
+                uint64_t head = (uint64_t)own | (uint64_t)d << 16;
+                if (!long_head) {
+                    // (The third and fourth u16 are entries 4 and 5.)
+                    head |= (four(e + 4, std::min(m - 4, 2), pad) << 32);
+                } else if (p.bsg == 1) {
+                    head |= (uint64_t)(own + n) << 48;
+                } else {
+                    const int pos = std::min(std::max(s->npos[i] - q0, 0), m);
+                    head |= (uint64_t)(((1u << m) - 1u) & ~((1u << pos) - 1u)) << 48;
                 }
-                best->push_back(int2{(draw_at[c2] + 64 * t) * 16, pa::item_word(63, 64 * t, 1, 0, kind)});
-            }
-        }
-        for (size_t v = 0; v < iv.size(); ++v) {
-            const bool chunk_end = v + 1 == iv.size(), sweep_end = chunk_end && c + 1 == n_chunks;
-            // (The sweep's last barrier is the kernel's own.)
-            const int flags = (sweep_end ? 0 : pa::kItemBarrier) | (chunk_end && !p.fuse ? pa::kItemChunk : 0);
-            for (int w = 0; w < nw; ++w) {
-                auto &it = iv[v].wave[w];
-                if (flags != 0) {
-                    if (it.empty()) it.push_back(int2{0, pa::item_word(0, 0, 1, 0, 0)});
-                    it.back().y |= pa::item_word(0, 0, 1, 0, flags);
+                put(h, head);
+                put(h + 4, four(e, m, pad));
+                uint16_t *b = h + stride;
+                for (int r = 1, t = e0; r < it.rows; ++r, b += stride, t += 8) {
+                    put(b, four(e + t, m - t, pad));
+                    put(b + 4, four(e + t + 4, m - t - 4, pad));
                 }
-                st[w].insert(st[w].end(), it.begin(), it.end());
             }
         }
-    }
-    p.items.clear();
-    p.streams.clear();
-    for (int w = 0; w < nw; ++w) {
-        std::vector<int2> &it = st[w];
-        if (it.size() & 1) it.push_back(int2{0, pa::item_word(0, 0, 1, 0, 0)});
-        const size_t len = it.size();
-        p.streams.insert(p.streams.end(), {(int)p.items.size() / 2, (int)len, draw_at[0], draw_items[0]});
-        for (int q = 0; q < 3; ++q) it.push_back(len ? it[q % len] : int2{0, pa::item_word(0, 0, 1, 0, 0)});
-        for (const int2 &v : it) p.items.insert(p.items.end(), {v.x, v.y});
     }
 }
 
@@ -705,13 +767,13 @@ static size_t general_bytes(const pa_solver *s, const Plan &p)
         while (capk < need) capk += 8;
         blocks = 4 * (((size_t)(n + p.threads) * (2 + capk) + 32 + 1) / 2);
         for (int l = 0; l < p.n_levels; ++l)
-            stream += 16 * (size_t)((p.level_off[l + 1] - p.level_off[l] + p.threads - 1) / p.threads);
+            stream += 16 * (size_t)parts(p.level_off[l + 1] - p.level_off[l], p.threads);
     } else {
         const int NS = 64 / p.W, NW = p.threads / 64;
         blocks = 4 * ((size_t)n * (4 + 4 * ((std::max(s->dmax, 1) + 3) / 4)) + 32);
         size_t passes = 0;
         for (int l = 0; l < p.n_levels; ++l)
-            passes += (size_t)((p.level_off[l + 1] - p.level_off[l] + NW * NS - 1) / (NW * NS));
+            passes += (size_t)parts(p.level_off[l + 1] - p.level_off[l], NW * NS);
         stream = 8 * (size_t)NW * (passes + 4);
     }
     return align_up(sizeof(int) * n) + align_up(sizeof(int) * (p.n_levels + 1)) + align_up(blocks) +
@@ -720,8 +782,8 @@ static size_t general_bytes(const pa_solver *s, const Plan &p)
 
 static size_t tile_bytes(const pa_solver *s, const Plan &p)
 {
-    return align_up(sizeof(uint32_t) * p.blocks.size()) + align_up(sizeof(int) * p.items.size()) +
-           align_up(sizeof(int) * p.streams.size()) + tail_bytes(s, p, sizeof(uint32_t));
+    return align_up(p.row_bytes) + align_up(sizeof(int) * p.item_ints) + align_up(sizeof(int) * p.streams.size()) +
+           tail_bytes(s, p, sizeof(uint32_t));
 }
 
 // A compute unit holds 24 to 32 waves of the tile kernel; a workgroup takes its
@@ -814,7 +876,7 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
 }
 
 pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan &p, bool tables,
-                              const Shape *force, size_t room)
+                              const Shape *force, size_t room, const Levels *levels)
 {
     const int n = s->n;
     p.K = sch->n_steps;
@@ -924,12 +986,13 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
         p.W = force->W;
         p.threads = force->threads;
         p.nblk = (R + p.W - 1) / p.W;
-        build_levels(s, sch->order, p);
+        if (levels) static_cast<Levels &>(p) = *levels;
+        else build_levels(s, sch->order, p);
         if (force->ahead) {
             p.ahead = 1;
             p.deg = force->deg;
             p.fuse = force->fuse;
-            build_tile_plan(s, p);
+            build_tile_plan(s, p, tables);
             if (force->byte_threads != 0) {
                 Plan q;
                 q.kind = 1;
@@ -1029,7 +1092,7 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
         const size_t general = general_bytes(s, p);
         Plan q = p;
         if (take_tile_form(s, sch, q, cus, max_lds)) {
-            build_tile_plan(s, q);
+            build_tile_plan(s, q, tables);
             const size_t own = tile_bytes(s, q);
             p = std::move(q);
             p.pad = general > own ? general - own : 0;
@@ -1160,8 +1223,8 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
     L.qtab = sch->nl_period > 0 && sch->nl_kind == 1 ? take(sizeof(uint64_t) * (size_t)p.K * p.lmax1) : 0;
     L.sched = p.ahead ? 0 : take(sizeof(int) * n);
     L.level_off = p.ahead ? 0 : take(sizeof(int) * (p.n_levels + 1));
-    L.blocks = take(sizeof(uint32_t) * p.blocks.size());
-    L.stream = take(sizeof(int) * (p.ahead ? p.items.size() : p.kind == 1 ? p.rounds.size() : p.stream.size()));
+    L.blocks = take(p.ahead ? p.row_bytes : sizeof(uint32_t) * p.blocks.size());
+    L.stream = take(sizeof(int) * (p.ahead ? p.item_ints : p.kind == 1 ? p.rounds.size() : p.stream.size()));
     L.streams = p.ahead ? take(sizeof(int) * p.streams.size()) : 0;
     L.thr = take((p.ahead ? sizeof(uint32_t) : sizeof(uint64_t)) * (size_t)p.K * p.lmax1 * (s->dmax + 1));
     L.wtab = take(sizeof(uint64_t) * (size_t)total);
@@ -1311,14 +1374,17 @@ pa_status pa_host::start_run(pa_solver *s, const pa_schedule *sch, int32_t R, ui
         put(L.sched, P.sched.data(), sizeof(int) * n);
         put(L.level_off, P.level_off.data(), sizeof(int) * (P.n_levels + 1));
     }
-    put(L.blocks, P.blocks.data(), sizeof(uint32_t) * P.blocks.size());
     if (P.ahead) {
+        put(L.blocks, P.rows.data(), P.row_bytes);
         put(L.stream, P.items.data(), sizeof(int) * P.items.size());
         put(L.streams, P.streams.data(), sizeof(int) * P.streams.size());
-    } else if (P.kind == 1)
-        put(L.stream, P.rounds.data(), sizeof(int) * P.rounds.size());
-    else
-        put(L.stream, P.stream.data(), sizeof(int) * P.stream.size());
+    } else {
+        put(L.blocks, P.blocks.data(), sizeof(uint32_t) * P.blocks.size());
+        if (P.kind == 1)
+            put(L.stream, P.rounds.data(), sizeof(int) * P.rounds.size());
+        else
+            put(L.stream, P.stream.data(), sizeof(int) * P.stream.size());
+    }
     put(L.qtab, P.qtab.data(), sizeof(uint64_t) * P.qtab.size());
     if (P.kind == 1)
         put(L.thr, P.thr32.data(), sizeof(uint32_t) * P.thr32.size());

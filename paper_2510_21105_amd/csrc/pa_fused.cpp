@@ -127,10 +127,10 @@ namespace {
 constexpr int kTileCand[] = {4, 8, 16};
 
 // Plan a run with a shape without tables (sizes only).
-pa_status plan_size(pa_fused::Run &r, const Shape &sh, size_t *bytes)
+pa_status plan_size(pa_fused::Run &r, const Levels &levels, const Shape &sh, size_t *bytes)
 {
     Plan p;
-    const pa_status st = build_plan(r.s, &r.sch, r.R, p, false, &sh);
+    const pa_status st = build_plan(r.s, &r.sch, r.R, p, false, &sh, (size_t)-1, &levels);
     if (st == PA_OK) *bytes = p.L.total;
     return st;
 }
@@ -321,7 +321,8 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
 
     // Every run is planned once with the narrowest tile (what a shared launch
     // refuses is refused here), for its levels.
-    std::vector<int> fuse(count, 0), levels(count, 1);
+    std::vector<int> fuse(count, 0);
+    std::vector<Levels> levels(count);
     for (int i = 0; i < count; ++i) {
         pa_fused::Run &r = f->runs[i];
         Shape probe;
@@ -338,8 +339,8 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
             std::snprintf(msg, sizeof msg, "%s", pa_last_error());
             return bail(fail(st, "pa_fused_create: run %d: %s", i, msg));
         }
-        levels[i] = p.n_levels;
-        fuse[i] = fuse_draws(r.s, p.n_levels);
+        levels[i] = std::move(p);
+        fuse[i] = fuse_draws(r.s, levels[i].n_levels);
     }
     int cus = 256, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -368,7 +369,7 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
                 deg = std::max(deg, degree_class(f->runs[i].s->dmax));
                 all_fuse &= fuse[i];
                 nodes += f->runs[i].s->n;
-                lvls += levels[i];
+                lvls += levels[i].n_levels;
             }
         if (g.members.empty()) continue;
         std::stable_sort(g.members.begin(), g.members.end(),
@@ -416,7 +417,7 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
             size_t need = 0;
             for (const Shape &c : g.candidates) {
                 size_t b = 0;
-                pa_status st = plan_size(r, c, &b);
+                pa_status st = plan_size(r, levels[i], c, &b);
                 if (st != PA_OK) {
                     char msg[400];
                     std::snprintf(msg, sizeof msg, "%s", pa_last_error());

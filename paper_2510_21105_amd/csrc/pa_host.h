@@ -51,9 +51,16 @@ struct Layout {
     size_t counts, xinit, total;
 };
 
-struct Plan {
+// The sweep order's dependency levels: level l is nodes sched[level_off[l] ..
+// level_off[l + 1]).
+struct Levels {
+    int n_levels = 0;
+    std::vector<int> sched, level_off;
+};
+
+struct Plan : Levels {
     int K = 0, S = 0, R = 0, G = 0, Rp = 0, W = 0, threads = 0, nblk = 0, nw32 = 0;
-    int lmax1 = 1, n_levels = 0, record = 0;
+    int lmax1 = 1, record = 0;
     int kind = 2, sgn = 0, block_bytes = 0, qpad = 0, n_rounds = 0, flush_every = 1;
     int direct = 0;   // kernel 1: block entries are LDS byte offsets (else record indices)
     int prio_mode = 0;  // kernel 1: issue-priority turns (SweepArgs::prio_mode)
@@ -63,11 +70,12 @@ struct Plan {
     int fuse = 0;     //   draws in registers, no draw buffer
     int draw_half = 0;  // SweepArgs::draw_half
     size_t pad = 0;     // bytes of the workspace left over at its end
-    std::vector<int> sched, level_off;
     std::vector<uint32_t> blocks;   // [n][block_bytes / 4] + 128 B
     std::vector<int> stream;        // kernel 2: [waves][qpad][2]
     std::vector<int> rounds;        // kernel 1: [n_rounds][4]
+    std::vector<uint16_t> rows;         // tile form: the blocks
     std::vector<int> items, streams;    // tile form: SweepArgs::items, streams
+    size_t row_bytes = 0, item_ints = 0;    // sizes of rows and items, known also where they are not filled
     std::vector<uint64_t> thr, wtab;
     std::vector<uint32_t> thr32;   // kernel 1: [K][lmax1][dmax + 1] = T[1..dmax], saturation flag
     std::vector<uint64_t> qtab;    // single-replica cluster moves: [K][lmax1] bond thresholds
@@ -97,8 +105,7 @@ struct Shape {
         return {W, bsg, ahead, direct, deg, fuse, threads, blocks, lds};
     }
 };
-// The sweep order's dependency levels (Plan::n_levels, level_off, sched).
-void build_levels(const pa_solver *s, const int32_t *order, Plan &p);
+void build_levels(const pa_solver *s, const int32_t *order, Levels &p);
 // Threads of a tile-form workgroup of `lds` bytes where `need` of them come to
 // a compute unit.
 int tile_threads(int need, int lds, int max_lds, long long per_level, int fuse);
@@ -110,9 +117,11 @@ bool fuse_draws(const pa_solver *s, int n_levels);
 
 pa_status check_schedule(const pa_solver *s, const pa_schedule *sch, int R);
 // room: workspace bytes at hand (a form that needs more than another is passed
-// over then; 0: the general forms only).
+// over then; 0: the general forms only). levels: the order's, for a shape
+// imposed, where the caller has them. Without tables a plan is for its sizes
+// alone.
 pa_status build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan &p, bool tables,
-                     const Shape *force = nullptr, size_t room = (size_t)-1);
+                     const Shape *force = nullptr, size_t room = (size_t)-1, const Levels *levels = nullptr);
 uint64_t run_key(const pa_solver *s, const pa_schedule *sch, int32_t R, uint64_t seed, uint32_t instance);
 pa_status start_run(pa_solver *s, const pa_schedule *sch, int32_t R, uint64_t seed, uint32_t instance,
                     void *workspace, size_t workspace_bytes, void *stream, bool fresh, bool pinned = true,

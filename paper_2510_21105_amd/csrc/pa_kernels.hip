@@ -1271,7 +1271,7 @@ __global__ __launch_bounds__(1024) void sweep_bytes_multi_kernel(const MultiRun 
 // of a level to decide, or 64 slots of the next chunk to draw, and where a
 // barrier or a change of buffer half follows. An item's block holds, row by
 // row, one uint4 per lane (coalesced): u16 {record, degree} and, for signed
-// graphs, {node, sign bits or complement record}, then the neighbours' record
+// graphs, {0, sign bits or complement record}, then the neighbours' record
 // numbers, padded with the node's own record (x ^ x adds nothing); a draw
 // item's block is the nodes' numbers. The FUSE form's has {record, node}, a
 // byte per neighbour that is ONE's where the weight is negative, and four

@@ -233,11 +233,12 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     byte.W = byte.lds(s->n, s->dmax) <= p->max_lds ? 8 : 4;
     byte.threads = 512;
     byte.direct = pa::kBytesRecBase + (size_t)(s->n + 1) * byte.W <= 0xFFFF;
-    Plan plan;
-    build_levels(s, j.sch.order, plan);
+    Levels levels;
+    build_levels(s, j.sch.order, levels);
     auto rounds_at = [&](int T) {
         long long n = 0;
-        for (int l = 0; l < plan.n_levels; ++l) n += (plan.level_off[l + 1] - plan.level_off[l] + T - 1) / T;
+        for (int l = 0; l < levels.n_levels; ++l)
+            n += (levels.level_off[l + 1] - levels.level_off[l] + T - 1) / T;
         return n;
     };
     const long long r512 = rounds_at(512);
@@ -250,17 +251,17 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     tile.deg = degree_class(s->dmax);
     tile.byte_W = byte.W;
     tile.byte_threads = byte.threads;
-    tile.fuse = fuse_draws(s, plan.n_levels);
+    tile.fuse = fuse_draws(s, levels.n_levels);
     if (tile.fuse) tile.bsg = 2;
-    tile.threads = tile_threads(1 << 16, tile.lds(s->n, s->dmax), p->max_lds, s->n / plan.n_levels, tile.fuse);
+    tile.threads = tile_threads(1 << 16, tile.lds(s->n, s->dmax), p->max_lds, s->n / levels.n_levels, tile.fuse);
     j.shape = tile;
-    plan = Plan();
-    st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape);
+    Plan plan;
+    st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape, (size_t)-1, &levels);
     if (st == PA_OK && j.shape.ahead && align_up(plan.L.total) > p->bytes - p->heap_off) {
         // No room for this form's plan: the byte form's may be smaller.
         j.shape = byte;
         plan = Plan();
-        st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape);
+        st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape, (size_t)-1, &levels);
     }
     if (st != PA_OK) return st;
     j.lds = j.shape.lds(s->n, s->dmax);
