@@ -808,6 +808,23 @@ int pa_host::tile_threads(int need, int lds, int max_lds, long long per_level, i
     return fit == 2 ? 768 : 512;
 }
 
+// Form. The tile form shortens the chain of a level (n = 7,000, degree 12,
+// R = 1,024: 272 -> 213; R = 4,096: 430 -> 392), spreads long rows over
+// lanes (n = 800, R = 1,024, degree 48, where rows run past the byte
+// form's registers: 2,870 -> 350; degree 200 on 1,000 nodes, the word
+// kernel before: 47,440 -> 1,700), and its nibble records let 8 replicas
+// stand where bytes leave room for 4 or for fewer workgroups (n = 12,000,
+// R = 4,096, degree 4: 608 -> 481). The byte form keeps levels of many
+// nodes where two of its 8-replica workgroups a compute unit are the whole
+// launch: they fill its waves without drawing ahead (R = 4,096, n = 7,000
+// in colouring order, degree 12, 778 a level: 300, tile form 330; n =
+// 4,000, 444 a level: 217 with either; n = 7,000, degree 4, 467 a level: 320
+// and 308; R = 16,384, 778 a level: 1,186 and 1,163).
+bool pa_host::byte_form_wins(long long tiles8, int cus, long long per_level, int fuse, int dmax)
+{
+    return tiles8 > cus && tiles8 <= 2LL * cus && per_level > 480 && !fuse && dmax <= kBytesRegDegree;
+}
+
 // Whether a run takes the tile form, and its shape then; p comes with the
 // general form's choice and the levels. All figures: one step of 10 sweeps on
 // MI355X, microseconds.
@@ -816,7 +833,8 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
     const int n = s->n, tile = sch->tile_replicas;
     const bool sign_ok = n + 256 <= 0x7FFF;
     if (p.sgn && !sign_ok) return false;
-    const bool was_turns = p.kind == 1 && p.W == 8 && p.nblk > cus && p.nblk <= 2 * cus;
+    const bool byte8 = p.kind == 1 && p.W == 8;
+    const long long tiles8 = p.nblk;
     const long long per_level = n / p.n_levels;     // nodes a level, on average
     p.kind = 1;
     p.ahead = 1;
@@ -860,19 +878,7 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
             if (rounds_at(448) <= rounds_at(512)) p.threads = 448;
         }
     }
-    // Form. The tile form shortens the chain of a level (n = 7,000, degree 12,
-    // R = 1,024: 272 -> 213; R = 4,096: 430 -> 392), spreads long rows over
-    // lanes (n = 800, R = 1,024, degree 48, where rows run past the byte
-    // form's registers: 2,870 -> 350; degree 200 on 1,000 nodes, the word
-    // kernel before: 47,440 -> 1,700), and its nibble records let 8 replicas
-    // stand where bytes leave room for 4 or for fewer workgroups (n = 12,000,
-    // R = 4,096, degree 4: 608 -> 481). The byte form keeps levels of many
-    // nodes where two of its 8-replica workgroups a compute unit are the whole
-    // launch: they fill its waves without drawing ahead (R = 4,096, n = 7,000
-    // in colouring order, degree 12, 778 a level: 300, tile form 330; n =
-    // 4,000, 444 a level: 217 with either; n = 7,000, degree 4, 467 a level: 320
-    // and 308; R = 16,384, 778 a level: 1,186 and 1,163).
-    return !(was_turns && per_level > 480 && !p.fuse && s->dmax <= kBytesRegDegree);
+    return !(byte8 && byte_form_wins(tiles8, cus, per_level, p.fuse, s->dmax));
 }
 
 pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan &p, bool tables,

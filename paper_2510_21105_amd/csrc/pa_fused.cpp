@@ -121,6 +121,33 @@ int pa_host::device_max_lds()
     return 160 * 1024;
 }
 
+int pa_host::device_cus()
+{
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
+        return v;
+    (void)hipGetLastError();
+    return 256;
+}
+
+// Threads of a byte-form workgroup in a shared launch: the smallest of 64,
+// 128, 256, 512 that needs no more rounds (one barrier each) per sweep than
+// 512.
+int pa_host::byte_threads(const Levels &v)
+{
+    auto rounds_at = [&](int T) {
+        long long n = 0;
+        for (int l = 0; l < v.n_levels; ++l) n += (v.level_off[l + 1] - v.level_off[l] + T - 1) / T;
+        return n;
+    };
+    const long long r512 = rounds_at(512);
+    int threads = 512;
+    for (int T : {256, 128, 64})
+        if (rounds_at(T) <= r512) threads = T;
+    return threads;
+}
+
 namespace {
 
 // Tile widths the autotuner tries, each with 256, 512 and 1,024 threads.
@@ -342,12 +369,7 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
         levels[i] = std::move(p);
         fuse[i] = fuse_draws(r.s, levels[i].n_levels);
     }
-    int cus = 256, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
-        (void)hipGetLastError();
-        cus = 256;
-    }
+    const int cus = device_cus();
     long long tiles4 = 0, tiles8 = 0;            // workgroups of a step, all groups
     for (int i = 0; i < count; ++i) {
         tiles4 += (f->runs[i].R + 3) / 4;
@@ -397,6 +419,21 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
                 if (T0 == 768) T0 = 512;
                 g.candidates.push_back(sh);
             }
+        // Levels of many nodes are the byte form's too (byte_form_wins): one
+        // shape of it, untuned only where all workgroups of the batch are up to
+        // two a compute unit (one run of 7,000 nodes in colouring order, R =
+        // 4,096, 20 steps, whole call: 8.4 ms in the tile form, 7.2 in this).
+        Shape byte;
+        byte.bsg = bsg;
+        byte.threads = 64;
+        bool byte_ok = !all_fuse && per_level > 480;
+        for (int i : g.members) {
+            const pa_solver *s = f->runs[i].s;
+            byte_ok &= 2 * byte.lds(s->n, s->dmax) <= f->max_lds && s->dmax <= kBytesRegDegree;
+            byte.threads = std::max(byte.threads, byte_threads(levels[i]));
+            byte.direct &= pa::kBytesRecBase + (size_t)(s->n + 1) * byte.W <= 0xFFFF;
+        }
+        if (byte_ok) g.candidates.push_back(byte);
         if (g.candidates.empty())
             return bail(fail(PA_ERANGE, "pa_fused_create: a graph does not fit LDS at any shared shape"));
         // Untuned shape: 8 replicas per workgroup (4 where all workgroups of
@@ -404,7 +441,8 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
         // when they fit, else the first fit.
         g.shape = g.candidates[0];
         for (const Shape &c : g.candidates)
-            if (c.W == want && c.threads == T0) g.shape = c;
+            if (c.ahead && c.W == want && c.threads == T0) g.shape = c;
+        if (byte_ok && byte_form_wins(tiles8, cus, per_level, all_fuse, kBytesRegDegree)) g.shape = byte;
         f->groups.push_back(std::move(g));
     }
 

@@ -110,6 +110,10 @@ void build_levels(const pa_solver *s, const int32_t *order, Levels &p);
 // a compute unit.
 int tile_threads(int need, int lds, int max_lds, long long per_level, int fuse);
 
+// Whether the byte form steps `tiles8` workgroups of 8 replicas faster than
+// the tile form.
+bool byte_form_wins(long long tiles8, int cus, long long per_level, int fuse, int dmax);
+
 // Counter class of the tile form for a maximum degree.
 inline int degree_class(int dmax) { return dmax <= 63 ? 0 : dmax <= 127 ? 1 : 2; }
 // Whether the tile form draws in registers for this graph and order.
@@ -133,6 +137,10 @@ std::vector<int2> multi_work_list(const std::vector<int> &nblk, int W);
 void finish_run(pa_solver *s, hipStream_t hs);
 // The largest dynamic LDS of a workgroup on the current device.
 int device_max_lds();
+// Compute units of the current device.
+int device_cus();
+// Threads of a byte-form workgroup in a shared launch.
+int byte_threads(const Levels &v);
 
 }  // namespace pa_host
 
