@@ -61,7 +61,11 @@ struct pa_pool {
         int32_t R = 0;
         uint64_t seed = 0;
         uint32_t inst = 0;
-        Shape shape;
+        Shape by_load[3];              // the tile form's, for one, two and more workgroups a compute unit
+        Shape byte;                    // the byte form's
+        bool byte_only = false;
+        long long per_level = 1;       // nodes a level, on average
+        Shape shape;                   // taken on admission, with:
         Key key;
         int lds = 0;
         size_t need = 0, off = 0;
@@ -94,7 +98,7 @@ struct pa_pool {
     std::map<int64_t, Job> jobs;
     std::deque<int64_t> waiting;
     int64_t next_ticket = 1;
-    int max_lds = 160 * 1024;
+    int max_lds = 160 * 1024, cus = 256;
     hipStream_t stream = nullptr;
     bool have_stream = false;
     hipEvent_t setup_ev = nullptr;
@@ -168,6 +172,7 @@ extern "C" pa_status pa_pool_create(pa_pool **out, void *workspace, size_t works
     p->heap_off = fixed;
     p->free_[fixed] = (workspace_bytes - fixed) / kAlign * kAlign;
     p->max_lds = device_max_lds();
+    p->cus = device_cus();
     *out = p;
     return PA_OK;
 }
@@ -220,30 +225,21 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     j.seed = run->seed;
     j.inst = run->instance;
     j.K = run->schedule->n_steps;
-    // Shape: 8 replicas per workgroup in the tile form, with the threads of a
-    // busy compute unit (as many workgroups as its LDS holds); sign-bit entries
-    // for graphs with -1 weights. Where the pool is too small for that form's
-    // plan, the byte form: 8 replicas where a tile's records fit LDS, else 4,
-    // LDS offsets as entries where they fit 16 bits, and the smallest of 64,
-    // 128, 256, 512 threads whose rounds per sweep (one per dependency-level
-    // chunk) are no more than with 512.
+    // Shapes: 8 replicas per workgroup in the tile form, with the threads of a
+    // compute unit that holds one, two or more of them (choose_shape takes one
+    // by the load); sign-bit entries for graphs with -1 weights. The byte form
+    // has 8 replicas where a tile's records fit LDS, else 4, and LDS offsets as
+    // entries where they fit 16 bits; a pool too small for the tile form's plan
+    // takes the run in it.
     const pa_solver *s = run->solver;
-    Shape byte;
-    byte.bsg = s->has_neg ? 2 : 0;
-    byte.W = byte.lds(s->n, s->dmax) <= p->max_lds ? 8 : 4;
-    byte.threads = 512;
-    byte.direct = pa::kBytesRecBase + (size_t)(s->n + 1) * byte.W <= 0xFFFF;
     Levels levels;
     build_levels(s, j.sch.order, levels);
-    auto rounds_at = [&](int T) {
-        long long n = 0;
-        for (int l = 0; l < levels.n_levels; ++l)
-            n += (levels.level_off[l + 1] - levels.level_off[l] + T - 1) / T;
-        return n;
-    };
-    const long long r512 = rounds_at(512);
-    for (int T : {256, 128, 64})
-        if (rounds_at(T) <= r512) byte.threads = T;
+    j.per_level = s->n / levels.n_levels;
+    Shape &byte = j.byte;
+    byte.bsg = s->has_neg ? 2 : 0;
+    byte.W = byte.lds(s->n, s->dmax) <= p->max_lds ? 8 : 4;
+    byte.threads = byte_threads(levels);
+    byte.direct = pa::kBytesRecBase + (size_t)(s->n + 1) * byte.W <= 0xFFFF;
     Shape tile = byte;
     tile.ahead = 1;
     tile.W = 8;
@@ -253,26 +249,33 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     tile.byte_threads = byte.threads;
     tile.fuse = fuse_draws(s, levels.n_levels);
     if (tile.fuse) tile.bsg = 2;
-    tile.threads = tile_threads(1 << 16, tile.lds(s->n, s->dmax), p->max_lds, s->n / levels.n_levels, tile.fuse);
-    j.shape = tile;
-    Plan plan;
-    st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape, (size_t)-1, &levels);
-    if (st == PA_OK && j.shape.ahead && align_up(plan.L.total) > p->bytes - p->heap_off) {
-        // No room for this form's plan: the byte form's may be smaller.
-        j.shape = byte;
-        plan = Plan();
-        st = build_plan(j.s, &j.sch, j.R, plan, false, &j.shape, (size_t)-1, &levels);
+    // The run's memory has room for each of its shapes.
+    const size_t heap = p->bytes - p->heap_off;
+    size_t need = 0;
+    for (int c = 2; c >= 0; --c) {
+        tile.threads = tile_threads(c == 2 ? 1 << 16 : c + 1, tile.lds(s->n, s->dmax), p->max_lds, j.per_level,
+                                    tile.fuse);
+        j.by_load[c] = tile;
+        if (c < 2 && tile == j.by_load[c + 1]) continue;
+        Plan plan;
+        st = build_plan(j.s, &j.sch, j.R, plan, false, &tile, (size_t)-1, &levels);
+        if (st != PA_OK) return st;
+        const size_t b = align_up(plan.L.total);
+        if (c < 2 && b > heap) j.by_load[c] = j.by_load[c + 1];
+        else need = std::max(need, b);
     }
-    if (st != PA_OK) return st;
-    j.lds = j.shape.lds(s->n, s->dmax);
-    j.key.shape = j.shape;
-    j.key.shape.byte_W = j.key.shape.byte_threads = 0;
-    j.key.cls = std::min(j.shape.ahead ? 4 : 8, p->max_lds / std::max(j.lds, 1));
-    j.need = align_up(plan.L.total);
-    if (j.need > p->bytes - p->heap_off)
-        return fail(PA_EWORKSPACE, "run needs %zu bytes, more than the pool's %zu", j.need,
-                    p->bytes - p->heap_off);
-    if ((j.R + 63) / 64 * (64 / j.shape.W) + 64 * 8 > kLaneMaxWork)
+    if (need > heap) {
+        // No room for this form's plan: the byte form's may be smaller.
+        j.byte_only = true;
+        Plan plan;
+        st = build_plan(j.s, &j.sch, j.R, plan, false, &byte, (size_t)-1, &levels);
+        if (st != PA_OK) return st;
+        need = align_up(plan.L.total);
+    }
+    j.need = need;
+    if (j.need > heap)
+        return fail(PA_EWORKSPACE, "run needs %zu bytes, more than the pool's %zu", j.need, heap);
+    if ((j.R + 63) / 64 * (64 / (j.byte_only ? byte.W : 8)) + 64 * 8 > kLaneMaxWork)
         return fail(PA_ERANGE, "run of %d replicas exceeds a lane's work list", j.R);
     const int64_t t = p->next_ticket++;
     p->jobs.emplace(t, std::move(j));
@@ -304,6 +307,27 @@ int lane_work(const pa_pool *p, const pa_pool::Lane &L)
     return w;
 }
 
+// The shape of a run that is admitted now, by the workgroups that the waiting
+// and the stepping runs come to. Where each gets a compute unit to itself it
+// takes that unit's threads (one run of 20 steps, whole call: 7,000 nodes in
+// colouring order, R = 512: 9.1 ms with a busy unit's 512, 8.2 so, 9.0 in the
+// byte form; 12,000 nodes 12.8, 10.8 and 11.9), and up to two a unit may be the
+// byte form's (7,000 nodes, R = 4,096: 11.5 ms in the tile form, 10.4).
+void choose_shape(const pa_pool *p, pa_pool::Job &j)
+{
+    long long tiles8 = 0;
+    for (auto &kv : p->jobs)
+        if (kv.second.state < 2) tiles8 += (kv.second.R + 7) / 8;
+    const pa_solver *s = j.s;
+    const bool two = 2 * j.byte.lds(s->n, s->dmax) <= p->max_lds;
+    const bool byte = j.byte_only || (two && byte_form_wins(tiles8, p->cus, j.per_level, j.by_load[2].fuse, s->dmax));
+    j.shape = byte ? j.byte : j.by_load[tiles8 <= p->cus ? 0 : tiles8 <= 2LL * p->cus ? 1 : 2];
+    j.lds = j.shape.lds(s->n, s->dmax);
+    j.key.shape = j.shape;
+    j.key.shape.byte_W = j.key.shape.byte_threads = 0;
+    j.key.cls = std::min(j.shape.ahead ? 4 : 8, p->max_lds / std::max(j.lds, 1));
+}
+
 // Admit waiting runs in arrival order, without overtaking, while their
 // memory fits and their lane (an existing lane of their shape, else a free
 // one) has room; set them up on the pool's stream `hs`.
@@ -312,6 +336,7 @@ pa_status admit(pa_pool *p, hipStream_t hs)
     bool any = false;
     while (!p->waiting.empty()) {
         pa_pool::Job &j = p->jobs.at(p->waiting.front());
+        choose_shape(p, j);
         int li = -1;
         for (int q = 0; q < kLanes && li < 0; ++q)
             if (p->lanes[q].used && p->lanes[q].key == j.key) li = q;

@@ -53,3 +53,34 @@ def test_fused_batch_keeps_the_byte_form_on_large_levels(pa, R, byte, tune):  # 
         assert (fb.info()[0]["lds_bytes"] == _byte_lds(1000, 8)) == byte, fb.info()
     fb.run()
     _check_against_oracle(s, wl, p)
+
+def _pooled(pa, wls):
+    """The runs submitted together to one pool and stepped to the end: their solvers."""
+    import torch
+    pool = pa.Pool(256 << 20)
+    stream = torch.cuda.Stream()
+    solvers = [pa.Solver(w["graph"]) for w in wls]
+    for s, w in zip(solvers, wls):
+        pool.submit(s, pa.params_from_workload(w, record=3))
+    while pool.info()["waiting"] or pool.info()["stepping"]:
+        pool.advance(stream, 4)
+    torch.cuda.synchronize()
+    assert len(pool.poll()) == len(wls)
+    out = []
+    for s, w in zip(solvers, wls):
+        _check_against_oracle(s, w, pa.params_from_workload(w, record=3))
+        out.append(s.launch_info())
+    pool.close()
+    return out
+
+def test_pooled_run_takes_threads_by_the_load(pa):  # noqa: F811
+    """A run alone in the pool whose workgroups get a compute unit each takes
+    more threads than the same run among many; in between, on large levels, the
+    byte form. Results are the oracle's every time."""
+    g = _two_levels(1000, 13, False)
+    few = [_wl(g, 100, (0.1, 0.9, 2.0), inst=q) for q in range(2)]
+    alone = _pooled(pa, few[:1])[0]
+    both = _pooled(pa, [few[0], _wl(W.torus(12, 3, True), 2500, (0.1,), sweeps=1)])[0]
+    crowd = _pooled(pa, [few[1], _wl(W.torus(12, 3, True), 6000, (0.1,), sweeps=1)])[0]
+    assert both["lds_bytes"] == _byte_lds(1000, 8) < min(alone["lds_bytes"], crowd["lds_bytes"])
+    assert alone["threads"] > crowd["threads"]
