@@ -3325,10 +3325,15 @@ int launch_sweep_multi(const MultiShape &sh, const MultiRun *runs, const int2 *w
 // Threads of a step's epilogue: its chain of barriers is shorter with fewer
 // waves (R = 128: 52.5 us a whole step of 10 sweeps on 20 nodes with 1,024
 // threads, 49.4 with 128; R = 4,096, n = 7,000: 400 and 398 with 512), its loops
-// with more (R = 16,384: 621 with 512, 609). Adaptive steps try a jump a wave.
-static int epilogue_threads(int R, bool adapt)
+// with more (R = 16,384: 621 with 512, 609). Adaptive steps try a jump a wave,
+// jump 1 untried: past 9 jumps 8 waves take two passes, past 17 three (mean of
+// the epilogues of a run on 20 nodes, 512 and 1,024 threads, 16 jumps: R = 512
+// 4.4 us and 5.0, R = 2,048 6.8 and 6.9, R = 4,096 9.6 and 8.9; 64 jumps: R =
+// 512 4.6 and 4.7, R = 1,024 5.8 and 5.5, R = 4,096 12.0 and 10.1).
+static int epilogue_threads(int R, int adapt_jump)
 {
-    return R <= 512 && !adapt ? 128 : R <= 8192 ? 512 : kMaxThreads;
+    if (R > 8192 || (R > 2048 && adapt_jump > 9) || (R > 512 && adapt_jump > 17)) return kMaxThreads;
+    return R > 512 || adapt_jump > 0 ? 512 : 128;
 }
 
 int launch_epilogue_multi(int runs_count, int max_R, const MultiRun *runs, int k, void *stream)
@@ -3338,7 +3343,7 @@ int launch_epilogue_multi(int runs_count, int max_R, const MultiRun *runs, int k
     if (allow_lds(reinterpret_cast<const void *>(&epilogue_multi_kernel), configured, lds,
                   "hipFuncSetAttribute(epilogue_multi)"))
         return -1;
-    hipLaunchKernelGGL(epilogue_multi_kernel, dim3(runs_count), dim3(epilogue_threads(max_R, false)), lds,
+    hipLaunchKernelGGL(epilogue_multi_kernel, dim3(runs_count), dim3(epilogue_threads(max_R, 0)), lds,
                        (hipStream_t)stream, runs, k);
     return check("epilogue_multi_kernel");
 }
@@ -3350,7 +3355,7 @@ int launch_epilogue(const EpiArgs &a, void *stream)
     if (allow_lds(reinterpret_cast<const void *>(&epilogue_kernel), configured, lds,
                   "hipFuncSetAttribute(epilogue)"))
         return -1;
-    hipLaunchKernelGGL(epilogue_kernel, dim3(1), dim3(epilogue_threads(a.R, a.adapt != 0)), lds,
+    hipLaunchKernelGGL(epilogue_kernel, dim3(1), dim3(epilogue_threads(a.R, a.adapt ? a.adapt_jump : 0)), lds,
                        (hipStream_t)stream, a);
     return check("epilogue_kernel");
 }

@@ -84,3 +84,11 @@ def test_pooled_run_takes_threads_by_the_load(pa):  # noqa: F811
     crowd = _pooled(pa, [few[1], _wl(W.torus(12, 3, True), 6000, (0.1,), sweeps=1)])[0]
     assert both["lds_bytes"] == _byte_lds(1000, 8) < min(alone["lds_bytes"], crowd["lds_bytes"])
     assert alone["threads"] > crowd["threads"]
+
+
+@pytest.mark.parametrize("R,jump", [(512, 64), (513, 17), (513, 18), (2048, 10), (2049, 9), (2049, 10), (8193, 64)])
+def test_adaptive_jumps_at_every_epilogue_width(pa, R, jump):  # noqa: F811
+    """One wave tries one jump: 8 or 16 waves, in one pass and in several."""
+    g = W.random_graph(40, 120, 3)
+    wl = _wl(g, R, np.linspace(0.05, 3.2, 80), beta_adapt=1, adapt_jump=jump)
+    _compare(pa, g, wl, record=0)
