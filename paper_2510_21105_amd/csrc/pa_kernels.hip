@@ -3291,9 +3291,15 @@ static int launch_multi_tile_t(const MultiShape &sh, const MultiRun *runs, const
 template <int W, int SG>
 static int launch_multi_w(const MultiShape &sh, const MultiRun *runs, const int2 *work, int k, void *stream)
 {
-    if (!sh.ahead)
-        return sh.direct ? launch_multi_t<W, SG, true>(sh, runs, work, k, stream)
-                         : launch_multi_t<W, SG, false>(sh, runs, work, k, stream);
+    if (!sh.ahead) {
+        if constexpr (W == 16) {
+            snprintf(g_err, sizeof g_err, "byte-form shared launches take 4 or 8 replicas");
+            return -1;
+        } else {
+            return sh.direct ? launch_multi_t<W, SG, true>(sh, runs, work, k, stream)
+                             : launch_multi_t<W, SG, false>(sh, runs, work, k, stream);
+        }
+    }
     if (sh.fuse) {
         if constexpr (W <= 8 && SG == 2) return launch_multi_tile_t<W, SG, 0, true>(sh, runs, work, k, stream);
         snprintf(g_err, sizeof g_err, "draws in registers take 4 or 8 replicas and sign bits");
