@@ -411,6 +411,50 @@ bool pa_host::fuse_draws(const pa_solver *s, int n_levels)
            s->n >= 256 * n_levels;
 }
 
+// Nodes of a level that a wave of the tile form takes together.
+struct Item {
+    int slot, count, lp, rows, per;     // per: entries a lane, of the largest node
+    int lanes() const { return count << lp; }
+};
+
+// The levels cut into items. Entries a lane's block holds: 6 + 8 after a short
+// header, 4 in the first row after a long one, 8 more with 16-bit counters (16
+// in all with sign bits), four with draws in registers. A node of a larger
+// degree takes 2^lp lanes. An item that leaves half its lanes free spreads its
+// nodes over more of them down to one row a lane: the chain of a level shortens
+// with the entries read in turn.
+static void cut_levels(const pa_solver *s, const Levels &v, bool long_head, bool d16, int fuse,
+                       std::vector<Item> &cut, int *level_item)
+{
+    const int e0 = long_head ? 4 : 6;
+    const int most = fuse ? e0 : !d16 ? e0 + 8 : long_head ? 16 : e0 + 16, lp_max = d16 ? 6 : 4;
+    cut.reserve(v.n_levels + s->n / 32);
+    for (int l = 0; l < v.n_levels; ++l) {
+        for (int t = v.level_off[l]; t < v.level_off[l + 1];) {
+            const int i = v.sched[t], md = s->row_ptr[i + 1] - s->row_ptr[i];
+            auto per_lane = [&](int lp) { return (md + (1 << lp) - 1) >> lp; };
+            Item it{t, 0, 0, 1, 0};
+            while (per_lane(it.lp) > most) ++it.lp;
+            it.count = std::min(v.level_off[l + 1] - t, 64 >> it.lp);
+            while (it.lp < lp_max && per_lane(it.lp) > e0 && it.count << (it.lp + 1) <= 64) ++it.lp;
+            it.per = per_lane(it.lp);
+            it.rows = it.per <= e0 ? 1 : 1 + (it.per - e0 + 7) / 8;
+            cut.push_back(it);
+            t += it.count;
+        }
+        if (level_item) level_item[l + 1] = (int)cut.size();
+    }
+}
+
+long long pa_host::tile_rows(const pa_solver *s, const Levels &v, bool long_head)
+{
+    std::vector<Item> cut;
+    cut_levels(s, v, long_head, s->dmax > kMaxBytesDegree, 0, cut, nullptr);
+    long long rows = 0;
+    for (const Item &it : cut) rows += it.rows;
+    return rows;
+}
+
 // The tile form's item streams and blocks (their layout is described at
 // sweep_tile_kernel). Every level is cut into items of at most 64 lanes, dealt over the
 // waves; levels are gathered into chunks whose draws fit half the draw buffer,
@@ -421,37 +465,11 @@ static void build_tile_plan(const pa_solver *s, Plan &p, bool fill)
 {
     const int n = s->n, W = p.W, nw = p.threads / 64;
     const bool d16 = p.deg == 2;
-    // Entries a lane's block holds: 6 + 8 after a short header, 4 in the first
-    // row after a long one, 8 more with 16-bit counters (16 in all with sign
-    // bits), four with draws in registers. A node of a larger degree takes
-    // 2^lp lanes. An item that leaves half its lanes free spreads its nodes
-    // over more of them down to one row a lane: the chain of a level shortens
-    // with the entries read in turn.
     const bool long_head = p.bsg != 0;
     const int e0 = long_head ? 4 : 6;
-    const int most = p.fuse ? e0 : !d16 ? e0 + 8 : p.bsg == 2 ? 16 : e0 + 16, lp_max = d16 ? 6 : 4;
-    struct Item {
-        int slot, count, lp, rows, per;     // per: entries a lane, of the largest node
-        int lanes() const { return count << lp; }
-    };
     std::vector<Item> cut;
-    cut.reserve(p.n_levels + n / 32);
     std::vector<int> level_item(p.n_levels + 1, 0);
-    for (int l = 0; l < p.n_levels; ++l) {
-        for (int t = p.level_off[l]; t < p.level_off[l + 1];) {
-            const int i = p.sched[t], md = s->row_ptr[i + 1] - s->row_ptr[i];
-            auto per_lane = [&](int lp) { return (md + (1 << lp) - 1) >> lp; };
-            Item it{t, 0, 0, 1, 0};
-            while (per_lane(it.lp) > most) ++it.lp;
-            it.count = std::min(p.level_off[l + 1] - t, 64 >> it.lp);
-            while (it.lp < lp_max && per_lane(it.lp) > e0 && it.count << (it.lp + 1) <= 64) ++it.lp;
-            it.per = per_lane(it.lp);
-            it.rows = it.per <= e0 ? 1 : 1 + (it.per - e0 + 7) / 8;
-            cut.push_back(it);
-            t += it.count;
-        }
-        level_item[l + 1] = (int)cut.size();
-    }
+    cut_levels(s, p, long_head, d16, p.fuse, cut, level_item.data());
     p.n_rounds = 0;
     for (int l = 0; l < p.n_levels; ++l) p.n_rounds += parts(level_item[l + 1] - level_item[l], nw);
 
@@ -808,21 +826,33 @@ int pa_host::tile_threads(int need, int lds, int max_lds, long long per_level, i
     return fit == 2 ? 768 : 512;
 }
 
-// Form. The tile form shortens the chain of a level (n = 7,000, degree 12,
-// R = 1,024: 272 -> 213; R = 4,096: 430 -> 392), spreads long rows over
-// lanes (n = 800, R = 1,024, degree 48, where rows run past the byte
-// form's registers: 2,870 -> 350; degree 200 on 1,000 nodes, the word
-// kernel before: 47,440 -> 1,700), and its nibble records let 8 replicas
-// stand where bytes leave room for 4 or for fewer workgroups (n = 12,000,
-// R = 4,096, degree 4: 608 -> 481). The byte form keeps levels of many
-// nodes where two of its 8-replica workgroups a compute unit are the whole
-// launch: they fill its waves without drawing ahead (R = 4,096, n = 7,000
-// in colouring order, degree 12, 778 a level: 300, tile form 330; n =
-// 4,000, 444 a level: 217 with either; n = 7,000, degree 4, 467 a level: 320
-// and 308; R = 16,384, 778 a level: 1,186 and 1,163).
-bool pa_host::byte_form_wins(long long tiles8, int cus, long long per_level, int fuse, int dmax)
+// Form. The tile form shortens the chain of a level, spreads long rows over
+// lanes, and its nibble records let 8 replicas stand where bytes leave room for
+// 4 or for fewer workgroups (us a launch of 10 sweeps, byte form, or word kernel
+// for degree 200, and tile form: n = 7,000, degree 12, R = 1,024: 257, 200, R =
+// 4,096: 392, 365, R = 16,384: 1,799, 1,155; n = 800, degree 48, R = 1,024:
+// 2,742, 330; n = 1,000, degree 200: 47,200, 1,710; n = 12,000, degree 4, R =
+// 4,096: 597, 433).
+// The byte form draws in the level's own pass, which costs less where a level
+// has work enough for all waves: with two 8-replica workgroups a compute unit
+// of either form (three of the tile form's win), when the tile form's levels
+// are more than 14 block rows of 64 lanes, on average (R = 4,096, colouring
+// orders, byte and tile form: n = 7,000, degree 12, 30 rows a level: 281, 301;
+// n = 9,000, degree 18, 48: 412, 474; n = 7,000, degree 4, 21: 251, 267; n =
+// 4,000, degree 12, 18: 191, 191; n = 3,000, degree 12, 14: 168, 157; natural
+// order, n = 7,000, degree 12, 9: 392, 365; R = 16,384, n = 9,900, degree 20, 52:
+// 1,981, 2,183). Rows of more than 30 entries run past its registers: a wave of
+// them a level is lost from 34 on (degree 20 on n = 4,000, 22 rows: 280, 256; on
+// 9,900: 498, 556), several from 43 on (degree 24 on 9,900: 627, 594).
+bool pa_host::byte_levels(long long rows, long long levels, int dmax)
 {
-    return tiles8 > cus && tiles8 <= 2LL * cus && per_level > 480 && !fuse && dmax <= kBytesRegDegree;
+    return (rows > 14 * levels && dmax <= 33) || (rows > 30 * levels && dmax <= 42);
+}
+
+bool pa_host::two_a_unit(long long tiles8, int cus, int max_lds, int tile_lds, int byte_lds)
+{
+    const long long need = (tiles8 + cus - 1) / cus;
+    return std::min<long long>(need, max_lds / tile_lds) == 2 && std::min<long long>(need, max_lds / byte_lds) == 2;
 }
 
 // Whether a run takes the tile form, and its shape then; p comes with the
@@ -834,7 +864,7 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
     const bool sign_ok = n + 256 <= 0x7FFF;
     if (p.sgn && !sign_ok) return false;
     const bool byte8 = p.kind == 1 && p.W == 8;
-    const long long tiles8 = p.nblk;
+    const int byte_lds = p.sweep_lds(s);
     const long long per_level = n / p.n_levels;     // nodes a level, on average
     p.kind = 1;
     p.ahead = 1;
@@ -878,7 +908,8 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
             if (rounds_at(448) <= rounds_at(512)) p.threads = 448;
         }
     }
-    return !(byte8 && byte_form_wins(tiles8, cus, per_level, p.fuse, s->dmax));
+    return !(byte8 && p.W == 8 && !p.fuse && two_a_unit(p.nblk, cus, max_lds, lds(8), byte_lds) &&
+             byte_levels(tile_rows(s, p, p.bsg != 0), p.n_levels, s->dmax));
 }
 
 pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan &p, bool tables,

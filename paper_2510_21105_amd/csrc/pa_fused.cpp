@@ -383,7 +383,8 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
         for (int sc = 3; sc >= 0; --sc) {
         pa_fused::Group g;
         g.bsg = bsg;
-        int T0 = 512, deg = 0, all_fuse = 1;
+        int T0 = 512, deg = 0, all_fuse = 1, dmax = 0;
+        long long rows = 0;
         double nodes = 0, lvls = 0;
         for (int i = 0; i < count; ++i)
             if ((f->runs[i].s->has_neg ? 2 : 0) == bsg && size_class(f->runs[i].s->n) == sc) {
@@ -392,6 +393,8 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
                 all_fuse &= fuse[i];
                 nodes += f->runs[i].s->n;
                 lvls += levels[i].n_levels;
+                rows += tile_rows(f->runs[i].s, levels[i], bsg != 0);
+                dmax = std::max(dmax, f->runs[i].s->dmax);
             }
         if (g.members.empty()) continue;
         std::stable_sort(g.members.begin(), g.members.end(),
@@ -419,20 +422,22 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
                 if (T0 == 768) T0 = 512;
                 g.candidates.push_back(sh);
             }
-        // Levels of many nodes are the byte form's too (byte_form_wins): one
-        // shape of it, untuned only where all workgroups of the batch are up to
-        // two a compute unit (one run of 7,000 nodes in colouring order, R =
+        // Large levels are the byte form's too (byte_levels): one shape of it,
+        // untuned only where all workgroups of the batch come to two a compute
+        // unit in either form (one run of 7,000 nodes in colouring order, R =
         // 4,096, 20 steps, whole call: 8.4 ms in the tile form, 7.2 in this).
         Shape byte;
         byte.bsg = bsg;
         byte.threads = 64;
-        bool byte_ok = !all_fuse && per_level > 480;
+        int byte_lds = 0, tile_lds = 0;
         for (int i : g.members) {
             const pa_solver *s = f->runs[i].s;
-            byte_ok &= 2 * byte.lds(s->n, s->dmax) <= f->max_lds && s->dmax <= kBytesRegDegree;
+            byte_lds = std::max(byte_lds, byte.lds(s->n, s->dmax));
+            tile_lds = std::max(tile_lds, pa::sweep_tile_lds(8, 0, s->n, 0));
             byte.threads = std::max(byte.threads, byte_threads(levels[i]));
             byte.direct &= pa::kBytesRecBase + (size_t)(s->n + 1) * byte.W <= 0xFFFF;
         }
+        const bool byte_ok = !all_fuse && byte_levels(rows, (long long)lvls, dmax) && byte_lds <= f->max_lds;
         if (byte_ok) g.candidates.push_back(byte);
         if (g.candidates.empty())
             return bail(fail(PA_ERANGE, "pa_fused_create: a graph does not fit LDS at any shared shape"));
@@ -442,7 +447,7 @@ extern "C" pa_status pa_fused_create(pa_fused **out, const pa_fused_entry *runs,
         g.shape = g.candidates[0];
         for (const Shape &c : g.candidates)
             if (c.ahead && c.W == want && c.threads == T0) g.shape = c;
-        if (byte_ok && byte_form_wins(tiles8, cus, per_level, all_fuse, kBytesRegDegree)) g.shape = byte;
+        if (byte_ok && two_a_unit(tiles8, cus, f->max_lds, tile_lds, byte_lds)) g.shape = byte;
         f->groups.push_back(std::move(g));
     }
 

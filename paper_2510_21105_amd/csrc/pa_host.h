@@ -35,7 +35,6 @@ pa_status hip_fail(hipError_t e, const char *what);
 constexpr int kMaxN = 32767;   // node ids and LDS word indices fit 16 bits
 constexpr int kMaxDegree = 4096;
 constexpr int kMaxBytesDegree = 127;   // byte counters of kernel 1 (2u must fit a byte)
-constexpr int kBytesRegDegree = 30;    // row entries that the byte form keeps in registers
 constexpr int kMaxWideDegree = 1023;   // 16-bit counters of the tile form: 64 lanes x 16 entries
 constexpr int kMaxR = 32768;
 constexpr size_t kAlign = 256;
@@ -110,9 +109,12 @@ void build_levels(const pa_solver *s, const int32_t *order, Levels &p);
 // a compute unit.
 int tile_threads(int need, int lds, int max_lds, long long per_level, int fuse);
 
-// Whether the byte form steps `tiles8` workgroups of 8 replicas faster than
-// the tile form.
-bool byte_form_wins(long long tiles8, int cus, long long per_level, int fuse, int dmax);
+// Block rows of 64 lanes that a sweep of the tile form takes.
+long long tile_rows(const pa_solver *s, const Levels &v, bool long_head);
+// Where the byte form is the faster one: levels of that many such rows, and
+// workgroups of 8 replicas two a compute unit in either form.
+bool byte_levels(long long rows, long long levels, int dmax);
+bool two_a_unit(long long tiles8, int cus, int max_lds, int tile_lds, int byte_lds);
 
 // Counter class of the tile form for a maximum degree.
 inline int degree_class(int dmax) { return dmax <= 63 ? 0 : dmax <= 127 ? 1 : 2; }

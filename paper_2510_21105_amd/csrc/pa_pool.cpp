@@ -64,7 +64,7 @@ struct pa_pool {
         Shape by_load[3];              // the tile form's, for one, two and more workgroups a compute unit
         Shape byte;                    // the byte form's
         bool byte_only = false;
-        long long per_level = 1;       // nodes a level, on average
+        bool large_levels = false;     // the byte form's where the load is two workgroups a compute unit
         Shape shape;                   // taken on admission, with:
         Key key;
         int lds = 0;
@@ -234,7 +234,6 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     const pa_solver *s = run->solver;
     Levels levels;
     build_levels(s, j.sch.order, levels);
-    j.per_level = s->n / levels.n_levels;
     Shape &byte = j.byte;
     byte.bsg = s->has_neg ? 2 : 0;
     byte.W = byte.lds(s->n, s->dmax) <= p->max_lds ? 8 : 4;
@@ -249,12 +248,13 @@ extern "C" pa_status pa_pool_submit(pa_pool *p, const pa_fused_entry *run, int64
     tile.byte_threads = byte.threads;
     tile.fuse = fuse_draws(s, levels.n_levels);
     if (tile.fuse) tile.bsg = 2;
+    else j.large_levels = byte.W == 8 && byte_levels(tile_rows(s, levels, byte.bsg != 0), levels.n_levels, s->dmax);
     // The run's memory has room for each of its shapes.
     const size_t heap = p->bytes - p->heap_off;
     size_t need = 0;
     for (int c = 2; c >= 0; --c) {
-        tile.threads = tile_threads(c == 2 ? 1 << 16 : c + 1, tile.lds(s->n, s->dmax), p->max_lds, j.per_level,
-                                    tile.fuse);
+        tile.threads = tile_threads(c == 2 ? 1 << 16 : c + 1, tile.lds(s->n, s->dmax), p->max_lds,
+                                    s->n / levels.n_levels, tile.fuse);
         j.by_load[c] = tile;
         if (c < 2 && tile == j.by_load[c + 1]) continue;
         Plan plan;
@@ -319,8 +319,9 @@ void choose_shape(const pa_pool *p, pa_pool::Job &j)
     for (auto &kv : p->jobs)
         if (kv.second.state < 2) tiles8 += (kv.second.R + 7) / 8;
     const pa_solver *s = j.s;
-    const bool two = 2 * j.byte.lds(s->n, s->dmax) <= p->max_lds;
-    const bool byte = j.byte_only || (two && byte_form_wins(tiles8, p->cus, j.per_level, j.by_load[2].fuse, s->dmax));
+    const bool byte = j.byte_only || (j.large_levels && two_a_unit(tiles8, p->cus, p->max_lds,
+                                                                   j.by_load[2].lds(s->n, s->dmax),
+                                                                   j.byte.lds(s->n, s->dmax)));
     j.shape = byte ? j.byte : j.by_load[tiles8 <= p->cus ? 0 : tiles8 <= 2LL * p->cus ? 1 : 2];
     j.lds = j.shape.lds(s->n, s->dmax);
     j.key.shape = j.shape;

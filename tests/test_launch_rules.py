@@ -39,10 +39,10 @@ def _byte_lds(n, tile, copies=False):
 @pytest.mark.parametrize("tune", [False, True])
 @pytest.mark.parametrize("R,byte", [(2040, False), (2057, True), (4096, True), (4104, False)])
 def test_fused_batch_keeps_the_byte_form_on_large_levels(pa, R, byte, tune):  # noqa: F811
-    """Up to two 8-replica workgroups a compute unit on levels of more than 480
-    nodes: the form that a run alone takes there, untuned; a tuned batch may
+    """Two 8-replica workgroups a compute unit on levels of work enough for all
+    waves: the form that a run alone takes there, untuned; a tuned batch may
     take either. Results are the oracle's with both."""
-    g = _two_levels(1000, 13, True)
+    g = _two_levels(2000, 13, True)
     wl = _wl(g, R, (0.1, 0.8, 1.9))
     p = pa.params_from_workload(wl, record=3)
     s = pa.Solver(g)
@@ -50,7 +50,7 @@ def test_fused_batch_keeps_the_byte_form_on_large_levels(pa, R, byte, tune):  # 
     if tune:
         fb.tune(probe_steps=1)
     else:
-        assert (fb.info()[0]["lds_bytes"] == _byte_lds(1000, 8)) == byte, fb.info()
+        assert (fb.info()[0]["lds_bytes"] == _byte_lds(2000, 8)) == byte, fb.info()
     fb.run()
     _check_against_oracle(s, wl, p)
 
@@ -77,14 +77,14 @@ def _pooled(pa, wls):
 
 def test_pooled_run_takes_threads_by_the_load(pa):  # noqa: F811
     """A run alone in the pool whose workgroups get a compute unit each takes
-    more threads than the same run among many; in between, on large levels, the
-    byte form. Results are the oracle's every time."""
-    g = _two_levels(1000, 13, False)
+    more threads than the same run among many; with two a unit and large levels
+    it takes the byte form. Results are the oracle's every time."""
+    g = _two_levels(2000, 13, False)
     few = [_wl(g, 100, (0.1, 0.9, 2.0), inst=q) for q in range(2)]
     alone = _pooled(pa, few[:1])[0]
     both = _pooled(pa, [few[0], _wl(W.torus(12, 3, True), 2500, (0.1,), sweeps=1)])[0]
     crowd = _pooled(pa, [few[1], _wl(W.torus(12, 3, True), 6000, (0.1,), sweeps=1)])[0]
-    assert both["lds_bytes"] == _byte_lds(1000, 8) < min(alone["lds_bytes"], crowd["lds_bytes"])
+    assert both["lds_bytes"] == _byte_lds(2000, 8) < min(alone["lds_bytes"], crowd["lds_bytes"])
     assert alone["threads"] > crowd["threads"]
 
 
@@ -109,15 +109,26 @@ def test_adaptive_jumps_at_every_epilogue_width(pa, R, jump):  # noqa: F811
 # unit on large levels): rows of every register count, unsigned records and
 # complemented copies, offsets and (above 8,063 nodes) indices as entries.
 @pytest.mark.parametrize("n,deg,R,signed", [
-    (1000, 5, 2049, False), (1000, 8, 3001, True), (1000, 13, 4090, False), (1000, 14, 4096, True),
-    (1000, 21, 4090, True), (1000, 22, 4096, False), (1000, 29, 4096, True), (1000, 30, 4090, False),
+    (2000, 5, 2049, False), (2000, 8, 3001, True), (2000, 13, 4090, False), (2000, 14, 4096, True),
+    (2000, 21, 4090, True), (2000, 22, 4096, False), (2000, 30, 4096, True), (2000, 33, 4090, False),
     (8200, 8, 2100, False)])
 def test_byte_form_on_large_levels(pa, n, deg, R, signed):  # noqa: F811
     g = _two_levels(n, deg, signed)
-    s, _ = _compare(pa, g, _wl(g, R, (0.0, 0.3, 1.7), sweeps=2 if n == 1000 else 1), record=0)
+    s, _ = _compare(pa, g, _wl(g, R, (0.0, 0.3, 1.7), sweeps=2 if n == 2000 else 1), record=0)
     info = s.launch_info()
     assert info["sweep_kernel"] == 1 and info["tile_replicas"] == 8
     assert info["lds_bytes"] == _byte_lds(n, 8, signed), info
+
+
+# One block row a level to either side of the line, and a degree to either
+# side: the other form.
+@pytest.mark.parametrize("n,deg,byte", [(1792, 6, False), (1794, 6, True), (2000, 33, True), (2000, 34, False),
+                                        (4000, 42, True), (4000, 43, False)])
+def test_form_by_rows_a_level_and_degree(pa, n, deg, byte):  # noqa: F811
+    g = _two_levels(n, deg, False)
+    s = pa.Solver(g)
+    s.run(pa.params_from_workload(_wl(g, 4096, (0.2,), sweeps=1)))
+    assert (s.launch_info()["lds_bytes"] == _byte_lds(n, 8)) == byte, s.launch_info()
 
 
 def test_byte_form_on_the_benchmark_graph_in_colouring_order(pa):  # noqa: F811
