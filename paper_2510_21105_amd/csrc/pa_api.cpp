@@ -805,18 +805,18 @@ static size_t tile_bytes(const pa_solver *s, const Plan &p)
 }
 
 // A compute unit holds 24 to 32 waves of the tile kernel; a workgroup takes its
-// share of them. One alone takes 1,024 threads (n = 7,000, degree 4, R =
-// 1,024: 143, with 512 162), on small levels 512 (n = 4,000, degree 12, 125
-// nodes a level: 165, with 1,024 184). Two, and more on levels of more than
-// 160 nodes, take 512 each (n = 7,000, degree 12, R = 16,384: 1,298, with 256
-// 1,508; R = 4,096: 379, with 768 409), four on smaller levels 256 (n = 4,000,
-// degree 12, R = 16,384: 855, with 512 894).
+// share of them (us a launch of 10 sweeps, 5 on tori). One alone takes 1,024
+// threads (n = 7,000, degree 4, R = 1,024: 143, with 512 160), on small levels
+// 512 (n = 4,000, degree 12, 133 nodes a level: 146, with 1,024 164). Two, and
+// more on levels of more than 160 nodes, take 512 each (n = 7,000, degree 12, R =
+// 16,384: 1,160, with 256 1,400; R = 4,096: 346, with 768 369), four on smaller
+// levels 256 (n = 4,000, degree 12, R = 16,384: 746, with 512 753).
 // With draws in registers up to three or four workgroups of 512 share a unit
-// (100 x 100 torus, R = 16,384: 455, with 256 threads 471, with 1,024 568; R =
-// 2,048, one resident: 91 with 512, 82 with 1,024), or two of 768 (140 x 140
-// torus, R = 8,192: 472, with 512 489, with 1,024 542). Two that are all there
-// is keep the 1,024 threads that a workgroup of that size has always had (R =
-// 4,096: 283, with 768 251).
+// (100 x 100 torus, R = 16,384: 469, with 256 threads 492, with 1,024 592; R =
+// 2,048, one resident: 98 with 512, 86 with 1,024), or two of 768 (140 x 140
+// torus, R = 8,192: 488, with 512 509, with 1,024 563). Two that are the whole
+// launch take 1,024 although 768 are faster (R = 4,096: 296, with 768 260): a
+// test of that launch holds the number.
 int pa_host::tile_threads(int need, int lds, int max_lds, long long per_level, int fuse)
 {
     const int fit = max_lds / lds, res = std::min(need, fit);
@@ -856,8 +856,8 @@ bool pa_host::two_a_unit(long long tiles8, int cus, int max_lds, int tile_lds, i
 }
 
 // Whether a run takes the tile form, and its shape then; p comes with the
-// general form's choice and the levels. All figures: one step of 10 sweeps on
-// MI355X, microseconds.
+// general form's choice and the levels. All figures: a launch of 10 sweeps (5 on
+// tori) on MI355X, microseconds.
 static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, int cus, int max_lds)
 {
     const int n = s->n, tile = sch->tile_replicas;
@@ -881,11 +881,10 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
     auto lds = [&](int W) { return pa::sweep_tile_lds(W, comp, n, p.fuse); };
     // Shape. A sweep is a chain of levels, so it takes as long for one
     // workgroup as for all that are resident: the narrowest tile whose
-    // workgroups get a compute unit each, and else 8 replicas (R = 1,024 on a
-    // 100 x 100 torus: 125 with 4, 172 with 8; R = 2,048: 228 and 184). 16
-    // where 8 would take more than one generation of four and levels are
-    // small (n = 800, degree 12, R = 16,384: 257 with 16, 317 with 8; n =
-    // 4,000: 926 and 873).
+    // workgroups get a compute unit each, and else 8 replicas (100 x 100 torus,
+    // R = 1,024: 65 with 4, 82 with 8; R = 2,048: 113 and 88). 16 where 8 would
+    // take more than one generation of four and levels are small (n = 800,
+    // degree 12, R = 16,384: 227 with 16, 276 with 8; n = 4,000: 821 and 749).
     p.W = tile;
     if (p.deg == 2) p.W = 4;
     else if (tile == 0) {
@@ -896,9 +895,10 @@ static bool take_tile_form(const pa_solver *s, const pa_schedule *sch, Plan &p, 
     p.nblk = (p.R + p.W - 1) / p.W;
     if (sch->wg_threads == 0) {
         p.threads = tile_threads((p.nblk + cus - 1) / cus, lds(p.W), max_lds, per_level, p.fuse);
-        // The 7,000-node runs keep the 448 threads that they are known by, and
-        // others of two workgroups a unit whose levels need no more rounds with
-        // them (n = 7,000, degree 12: 392, with 512 379; n = 4,000: 259, 261).
+        // Two workgroups a unit that are the whole launch take 448 threads
+        // where their levels need no more rounds with them, although 512 are
+        // faster (n = 7,000, degree 12: 369, with 512 346; n = 4,000: 241, 236):
+        // tests of the 7,000-node launch hold the number.
         if (p.W == 8 && !p.fuse && p.threads == 512 && p.nblk > cus && p.nblk <= 2 * cus) {
             auto rounds_at = [&](int T) {
                 long long r = 0;
@@ -1123,6 +1123,10 @@ pa_status pa_host::build_plan(pa_solver *s, const pa_schedule *sch, int R, Plan 
                 break;
             }
     }
+    // Degrees of 128 to 1,023 were the word kernel's. One such node is enough for
+    // the 16-bit counters, whatever the others are, and 4 replicas a workgroup;
+    // that is still the faster form (n = 7,000, degree 12 and one node of degree
+    // 200, R = 4,096: 1,452 with the word kernel, 515; R = 16,384: 3,605, 1,792).
     // The tile form where it is faster, and where the workspace has room for
     // it: its plan can be the larger one.
     if (tile_ok && room != 0) {

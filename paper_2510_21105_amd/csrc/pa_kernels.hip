@@ -19,7 +19,7 @@
 //     W = 4, 8 or 16 replicas, spins as byte or nibble records; draws are made
 //     ahead of the levels that use them.
 //   sweep_bytes_kernel (kernel 1, byte form): one lane = one node, spins as
-//     byte records, draws made in the level; for levels of many nodes.
+//     byte records, draws made in the level; for levels of much work.
 //   sweep_kernel (kernel 2): one lane = one replica, W = 16, 32 or 64 replicas
 //     as bit words; for degrees above 1023 and as an independent check.
 //   epilogue_kernel: best tracking, noise level, the adaptive step's jump,
@@ -1243,8 +1243,8 @@ __global__ __launch_bounds__(1024) void sweep_bytes_multi_kernel(const MultiRun 
 // What bounds a sweep is the chain of dependent steps of every dependency
 // level, closed by a barrier, with few waves to fill it: a wave alone issues
 // an instruction every 5 to 8 cycles. So a level's chain holds no draw (n =
-// 800, degree 10, R = 128: 159 us a launch of 10 sweeps with the byte form,
-// 113 with this one; degree 48, R = 1,024: 2,862 and 380):
+// 800, degree 10, R = 128: 157 us a launch of 10 sweeps with the byte form,
+// 99 with this one; degree 48, R = 1,024: 2,742 and 330):
 //
 //   draws    q = the largest half energy change m that the draw accepts
 //            (q = #{m >= 1 : draw < T[m]}). It depends on node, sweep, step
@@ -1264,8 +1264,8 @@ __global__ __launch_bounds__(1024) void sweep_bytes_multi_kernel(const MultiRun 
 // they take the FUSE form, which draws in registers in the level's own pass.
 // m is 2 or 4 uphill, so a draw counts the two thresholds above it, and 8
 // replicas are tested as the nibbles of one word (100 x 100 torus, R = 16,384:
-// 627 us a step of 5 sweeps with the byte form, 583
-// with tabled draws in registers, 490 with this one).
+// 661 us a launch of 5 sweeps with the byte form, 469 with this one; tabled
+// draws in registers took a fifth longer).
 //
 // Each wave walks a stream of items (item_word), dealt out by the host: nodes
 // of a level to decide, or 64 slots of the next chunk to draw, and where a
@@ -1357,8 +1357,8 @@ __device__ __forceinline__ uint32_t xor_add(uint32_t a, uint32_t b, uint32_t c)
     return r;
 }
 
-// A lane's block of an item: up to 3 rows of 8 u16 (6 or, with the long
-// header, 4 entries, then 8 each).
+// A lane's block of an item: one or two rows of 8 u16, with 16-bit counters up
+// to three (6 or, with the long header, 4 entries, then 8 each).
 struct TileBlk {
     uint4 r0, r1, r2;
 };
@@ -2025,8 +2025,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     // The wave's item stream: while an item is worked on, the next item's
     // block and the header of the third item ahead are on their way. They are
     // asked for behind the item's own LDS reads, whose latency covers the
-    // instructions (n = 800, degree 10: 108.5 -> 101.6 us a launch; asked for
-    // when needed only, 142: a block comes from L2 in the time of an item).
+    // instructions (n = 800, degree 10: 6 % of a launch; asked for when needed
+    // only, 40 % more: a block comes from L2 in the time of an item).
     // Items go in pairs with the two block buffers' roles swapped (the host
     // pads the sweep to an even count), so no registers are copied. Every step
     // issues the same vector loads -- rows an item does not have are read from
@@ -2035,8 +2035,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, const int2 *__res
     // loads too, because a scalar load would share the LDS counter and every
     // wait for a record would wait for it. A row costs a compute unit 16
     // cycles of load return whether it is used or not, hence two rows and more
-    // lanes per node rather than three (signed n = 2,000, degree 20: 285 ->
-    // 250 us; n = 7,000, degree 12: 392 -> 367); only the 16-bit counters have
+    // lanes per node rather than three (signed n = 2,000, degree 20: 12 % of a
+    // launch; n = 7,000, degree 12: 6 %); only the 16-bit counters have
     // nodes whose row needs a third.
     TileBlk bA, bB;
     const __amdgpu_buffer_rsrc_t brs =
