@@ -322,14 +322,16 @@ typedef struct pa_fused pa_fused;
  *   pa_fused_workspace_bytes  device bytes the batch needs (every run's state
  *                     and the batch's own argument and work-list tables).
  *   pa_fused_tune     measures, per group, each candidate launch shape (4, 8
- *                     or 16 replicas per workgroup x 64, 128, 256 or 512
- *                     threads, where the group's graphs fit LDS) on the
+ *                     or 16 replicas per workgroup x 256, 512 or 1,024
+ *                     threads, where the group's graphs fit LDS, and one more
+ *                     where the sweep order's levels are large) on the
  *                     first probe_steps (1..64) steps of the group's runs
  *                     inside `workspace` (two probes each), and keeps the
  *                     fastest. Synchronous (it waits for the probes); leaves
  *                     no valid results. Without it a default shape is used:
- *                     8 replicas per workgroup and the smallest thread count
- *                     that needs no more rounds per sweep than 512 threads.
+ *                     8 replicas per workgroup (4 where all workgroups of the
+ *                     batch get a compute unit each then) and threads by the
+ *                     number of workgroups and the size of the levels.
  *   pa_fused_run      enqueues the whole batch on `stream`: each run's setup
  *                     (inputs, initial population), then the step loop of
  *                     every group, captured once into a HIP graph (for this
@@ -369,8 +371,8 @@ typedef struct pa_pool pa_pool;
  * works inside a caller-owned device region (its HBM budget) and admits
  * submitted runs in arrival order, without overtaking, as their state fits
  * the memory left. Admitted runs of one launch shape (record mode, tile
- * width, entry form, threads, LDS occupancy class) form a lane with a stream
- * of its own; each iteration of a lane advances all its runs by one
+ * width, sweep form, threads by the load on admission, LDS occupancy class)
+ * form a lane with a stream of its own; each iteration of a lane advances all its runs by one
  * temperature step, each at its own step: one sweep launch over the replica
  * tiles of those runs and one epilogue launch with a workgroup per run.
  * Lanes progress independently. A run's population stays resident on the
