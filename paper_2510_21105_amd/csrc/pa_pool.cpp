@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <deque>
 #include <map>
@@ -307,17 +308,28 @@ int lane_work(const pa_pool *p, const pa_pool::Lane &L)
     return w;
 }
 
-// The shape of a run that is admitted now, by the workgroups that the waiting
-// and the stepping runs come to. Where each gets a compute unit to itself it
+// What a tile of the run still has to do: nodes and row entries visited.
+double work_left(const pa_pool *p, const pa_pool::Job &j)
+{
+    const int done = j.state == 1 ? p->lanes[j.lane].iter - j.k_off : 0;
+    return (double)(j.K - done) * j.sch.sweeps_per_step * ((double)j.s->n + (double)j.s->nnz);
+}
+
+// The shape of a run that is admitted now, by the workgroups of the waiting and
+// the stepping runs, those of a shorter run for its share of this one's time
+// (a queue of two small runs and one of 13,229 nodes: 31.8 ms with all counted
+// in full, 26.8 so, 29.6 in the byte form). Where each gets a compute unit to itself it
 // takes that unit's threads (one run of 20 steps, whole call: 7,000 nodes in
 // colouring order, R = 512: 9.1 ms with a busy unit's 512, 8.2 so, 9.0 in the
 // byte form; 12,000 nodes 12.8, 10.8 and 11.9), and up to two a unit may be the
 // byte form's (7,000 nodes, R = 4,096: 11.5 ms in the tile form, 10.4).
 void choose_shape(const pa_pool *p, pa_pool::Job &j)
 {
-    long long tiles8 = 0;
+    const double own = work_left(p, j);
+    double load = 0;
     for (auto &kv : p->jobs)
-        if (kv.second.state < 2) tiles8 += (kv.second.R + 7) / 8;
+        if (kv.second.state < 2) load += ((kv.second.R + 7) / 8) * std::min(1.0, work_left(p, kv.second) / own);
+    const long long tiles8 = (long long)std::ceil(load);
     const pa_solver *s = j.s;
     const bool byte = j.byte_only || (j.large_levels && two_a_unit(tiles8, p->cus, p->max_lds,
                                                                    j.by_load[2].lds(s->n, s->dmax),

@@ -81,11 +81,15 @@ def test_pooled_run_takes_threads_by_the_load(pa):  # noqa: F811
     it takes the byte form. Results are the oracle's every time."""
     g = _two_levels(2000, 13, False)
     few = [_wl(g, 100, (0.1, 0.9, 2.0), inst=q) for q in range(2)]
+    t, betas = W.torus(12, 3, True), np.linspace(0.1, 1.0, 10)
     alone = _pooled(pa, few[:1])[0]
-    both = _pooled(pa, [few[0], _wl(W.torus(12, 3, True), 2500, (0.1,), sweeps=1)])[0]
-    crowd = _pooled(pa, [few[1], _wl(W.torus(12, 3, True), 6000, (0.1,), sweeps=1)])[0]
+    both = _pooled(pa, [few[0], _wl(t, 2500, betas, sweeps=6)])[0]
+    crowd = _pooled(pa, [few[1], _wl(t, 6000, betas, sweeps=6)])[0]
     assert both["lds_bytes"] == _byte_lds(2000, 8) < min(alone["lds_bytes"], crowd["lds_bytes"])
     assert alone["threads"] > crowd["threads"]
+    # Runs that end long before it leave it alone for most of its time.
+    short = _pooled(pa, [few[0], _wl(t, 2500, (0.1,), sweeps=1)])[0]
+    assert (short["threads"], short["lds_bytes"]) == (alone["threads"], alone["lds_bytes"])
 
 
 @pytest.mark.parametrize("signed", [False, True])
